@@ -239,6 +239,31 @@ namespace fh {
 // Polygons of up to this many vertices pass them to the rule kernel by value.
 constexpr int kPolyByValue = 128;
 
+// A radial curve's or polygon's boundary parameters: K harmonics (a then b)
+// or K vertices (x then y) in coef; n boundary nodes, m radial nodes.
+constexpr int kRuleRadial = 0, kRulePolygon = 1;
+struct RuleRec {
+    int kind, K, panels, q, m;
+    int64_t n;
+    double r0;
+    std::vector<double> coef;
+    const double* glq;
+    const double* glm;
+};
+
+// The same on the device, for a launch over many rules: blk0 is the rule's
+// first block, coef the index of its first coefficient.
+struct RuleHead {
+    int kind, K, panels, q, m, blk0;
+    int64_t n, coef;
+    double r0;
+    const double* glq;
+    const double* glm;
+    double* x;
+    double* y;
+    double* w;
+};
+
 // The stable binning's sort of n (tile key, node index) pairs by the low
 // key_bits of the key, on the context stream, and its scratch bytes
 // (fh_field.hip).
@@ -262,11 +287,10 @@ struct fh_quad {
     double D = 0.0;
     bool bbox_valid = false;
     double bbox[4] = {0, 0, 0, 0};  // xmin, xmax, ymin, ymax
-    // Enqueues the rule kernels again, in place, from the boundary parameters
-    // the rule was made from (rules built by one launch with their
-    // parameters by value: radial curves and small polygons); empty for the
-    // others.
-    std::function<fh_status()> rebuild;
+    // The boundary parameters of a rule built by one launch with its
+    // parameters by value (radial curves and small polygons), from which a
+    // batched call rebuilds it in place; null for the others.
+    std::unique_ptr<fh::RuleRec> rule;
     // Computes the bounding box on the host when a call first needs it
     // (generated rules whose box comes from their boundary parameters);
     // empty: a device reduction over the nodes.
@@ -308,6 +332,11 @@ const InvPhiCheb& inv_phi_cheb_cached(fh_ctx* c, const EsKernel& k, double theta
 fh_status fft_plan(fh_ctx* c, int nf1, int nf2, int batch, FftPlan** out);
 fh_status fft_exec(fh_ctx* c, FftPlan* p, void* data);
 fh_status quad_alloc(fh_ctx* c, int64_t N, fh_quad** out);
+// The distinct rules of a batch (each with a RuleRec) as one table for
+// rules_launch; returns the byte offset of the coefficients in it.
+size_t rules_pack(int B, const fh_quad* const* qs, std::vector<char>& blob, int* R, int* blocks);
+// Computes the R rules of a device table again, in place, on c's stream.
+fh_status rules_launch(fh_ctx* c, const void* table, size_t coef_off, int R, int blocks);
 fh_status quad_bbox(fh_ctx* c, const fh_quad* q, double* bb);
 fh_status device_bbox(fh_ctx* c, const double* x, const double* y, int64_t n, double* bb);
 fh_status device_bbox2(fh_ctx* c, const double* x1, const double* y1, int64_t n1, double* bb1, const double* x2,

@@ -196,7 +196,8 @@ fh_status launch_t1_rows(fh_ctx* c, const LdsCols& lr, int reach, int B, int gro
 // The type-1 pipeline for B instances sharing one grid geometry; u is device
 // memory (B x n2 x n1).  With `capture`, the launch sequence is recorded into
 // a hipGraph keyed by everything baked into it and replayed.  With
-// `rebuild`, every rule's kernels run again first (inside the graph).
+// `rebuild`, every rule is computed again first (inside the graph, from the
+// table of boundary parameters that this call uploads).
 template <class R>
 fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* lambda, const double* z, int n1,
                       int n2, double h1, double h2, double xc, double yc, const int32_t* occ, R* u, bool capture,
@@ -295,6 +296,11 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     if (!fused) FH_TRY(fft_plan(c, gg.nf1, 0, (int)std::max<int64_t>(total_rows, 1), &fa));
     if (lc.C == 0) FH_TRY(fft_plan(c, gg.nf2, 0, n1 * B, &fb));
 
+    std::vector<char> rules;
+    size_t rules_coef = 0;
+    int nrules = 0, rule_blocks = 0;
+    if (rebuild) rules_coef = rules_pack(B, qs, rules, &nrules, &rule_blocks);
+
     FH_TRY(counters_ready(c, (int64_t)tpi * B));
     const size_t F_count = 2 * (size_t)std::max<int64_t>(total_rows, 1) * (fused ? n1 : gg.nf1);
     const size_t Z_count = lc.C > 0 ? 0 : 2 * (size_t)B * n1 * gg.nf2;
@@ -302,7 +308,7 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     size_t need = aligned_bytes(rs * F_count) + aligned_bytes(rs * Z_count) + E2_bytes +
                   spread_bytes(c, Ntot, gg, tpi * B, rs) + aligned_bytes(sizeof(InstParams) * B) +
                   aligned_bytes(sizeof(EpiInst) * B) + aligned_bytes(sizeof(int2) * B) +
-                  aligned_bytes(extra_bytes);
+                  aligned_bytes(rules.size()) + aligned_bytes(extra_bytes);
     FH_TRY(arena_reserve(c, need));
     R* F = c->arena.take<R>(F_count);
     R* Z = c->arena.take<R>(Z_count);
@@ -311,6 +317,7 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     InstParams* dinst = c->arena.take<InstParams>(B);
     EpiInst* depi = c->arena.take<EpiInst>(B);
     int2* drwin = c->arena.take<int2>(B);
+    char* drules = c->arena.take<char>(rules.size());
     if (extra) *extra = c->arena.take<char>(extra_bytes);
     if (!u) u = static_cast<R*>(*extra);
     const bool batched = B > 1;
@@ -320,11 +327,11 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
         if (ragged)
             FH_HIP(hipMemcpyAsync(drwin, rwin.data(), sizeof(int2) * B, hipMemcpyHostToDevice, c->stream));
     }
+    if (rebuild) FH_HIP(hipMemcpyAsync(drules, rules.data(), rules.size(), hipMemcpyHostToDevice, c->stream));
 
     auto run = [&]() -> fh_status {
         timing_mark(c, 0);
-        if (rebuild)
-            for (int b = 0; b < B; ++b) FH_TRY(qs[b]->rebuild());
+        if (rebuild) FH_TRY(rules_launch(c, drules, rules_coef, nrules, rule_blocks));
         if (fused) {
             FH_TRY(spread_items<R>(c, inst[0], batched ? dinst : nullptr, B, Ntot, gg, sb, pl.k.beta, pl.k.poly));
             FH_TRY(launch_t1_rows<R>(c, lr, reach, B, (gg.rows + lr.C - 1) / lr.C, gg, sb, n1, F));
@@ -368,9 +375,10 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
 
     // graph key: every pointer and size baked into the launches
     char key[512];
-    snprintf(key, sizeof(key), "%p|%zu|%d|%lld|%d|%d|%d|%d|%d|%d|%a|%a|%a|%a|%d|%d|%d|%p|%p|%d|%lld",
+    snprintf(key, sizeof(key), "%p|%zu|%d|%lld|%d|%d|%d|%d|%d|%d|%a|%a|%a|%a|%d|%d|%d|%p|%p|%d|%d|%zu|%lld",
              (void*)c->arena.base, c->arena.cap, B, (long long)Ntot, n1, n2, gg.nf1, gg.nf2, gg.W, gg.rows, h1, h2,
-             xc, yc, gg.T, gg.P, gg.method, (void*)u, (void*)c->tile_cnt, rebuild ? 1 : 0, (long long)total_rows);
+             xc, yc, gg.T, gg.P, gg.method, (void*)u, (void*)c->tile_cnt, nrules, rule_blocks, rules_coef,
+             (long long)total_rows);
     std::string k2(key);
     for (int b = 0; b < B; ++b) k2 += "|" + std::to_string(qs[b]->N);
     // Graphs are captured and replayed on a private stream (the caller's may
@@ -1062,7 +1070,7 @@ fh_status fh_field_grid_batch_rebuild(fh_ctx* c, int32_t B, fh_quad* const* q, c
         FH_TRY(check_grid(n1, n2, h1, h2, xc, yc));
         for (int b = 0; b < B; ++b) {
             FH_ARG(q[b] && q[b]->ctx->device == c->device, FH_ERR_INVALID_ARG, "quadrature %d NULL or on another device", b);
-            FH_ARG(static_cast<bool>(q[b]->rebuild), FH_ERR_UNSUPPORTED,
+            FH_ARG(static_cast<bool>(q[b]->rule), FH_ERR_UNSUPPORTED,
                    "quadrature %d cannot be rebuilt on the device (radial curves and polygons of up to %d vertices "
                    "can)",
                    b, kPolyByValue);

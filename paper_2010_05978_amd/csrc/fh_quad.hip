@@ -25,20 +25,40 @@ struct RadialParams {
     double b[kMaxFourier];
 };
 
-// Boundary node i of the star-shaped curve r(t)(cos t, sin t) and its
-// vector weight (W, V) = x'(t) omega.
-__device__ __forceinline__ void radial_node(const RadialParams& rp, const double* __restrict__ gl, int64_t n,
-                                            int64_t i, double& X, double& Y, double& W, double& V)
+// Angle and weight of boundary node i of n: Gauss-Legendre panels, or the
+// periodic trapezoid rule.
+__device__ __forceinline__ void radial_angle(int panels, int q, const double* __restrict__ gl, int64_t n, int64_t i,
+                                             double& t, double& om)
 {
-    double t, om;
-    if (rp.panels > 0) {
-        const int p = (int)(i / rp.q), k = (int)(i % rp.q);
-        t = (2.0 * kPi / rp.panels) * (p + 0.5 * (1.0 + gl[k]));
-        om = (kPi / rp.panels) * gl[rp.q + k];
+    if (panels > 0) {
+        const int p = (int)(i / q), k = (int)(i % q);
+        t = (2.0 * kPi / panels) * (p + 0.5 * (1.0 + gl[k]));
+        om = (kPi / panels) * gl[q + k];
     } else {
         t = 2.0 * kPi * (double)(i + 1) / (double)n;
         om = 2.0 * kPi / (double)n;
     }
+}
+
+// Point of the star-shaped curve r(t)(cos t, sin t) and its vector weight
+// (W, V) = x'(t) omega.
+__device__ __forceinline__ void radial_point(double t, double om, double r, double dr, double& X, double& Y,
+                                             double& W, double& V)
+{
+    double st, ct;
+    sincos(t, &st, &ct);
+    X = r * ct;
+    Y = r * st;
+    W = om * (dr * ct - r * st);
+    V = om * (dr * st + r * ct);
+}
+
+// Boundary node i of the star-shaped curve and its vector weight.
+__device__ __forceinline__ void radial_node(const RadialParams& rp, const double* __restrict__ gl, int64_t n,
+                                            int64_t i, double& X, double& Y, double& W, double& V)
+{
+    double t, om;
+    radial_angle(rp.panels, rp.q, gl, n, i, t, om);
     double r = rp.r0, dr = 0.0;
     for (int k = 1; k <= rp.K; ++k) {
         double s, c;
@@ -46,12 +66,7 @@ __device__ __forceinline__ void radial_node(const RadialParams& rp, const double
         r += rp.a[k - 1] * c + rp.b[k - 1] * s;
         dr += k * (rp.b[k - 1] * c - rp.a[k - 1] * s);
     }
-    double st, ct;
-    sincos(t, &st, &ct);
-    X = r * ct;
-    Y = r * st;
-    W = om * (dr * ct - r * st);
-    V = om * (dr * st + r * ct);
+    radial_point(t, om, r, dr, X, Y, W, V);
 }
 
 // General closed curve X(t) = sum_{k=0}^{K} ax_k cos kt + bx_k sin kt, Y(t)
@@ -135,18 +150,174 @@ __device__ __forceinline__ void curve_rule(const P& rp, const double* __restrict
     w[j] = al * wl * (Xi * sb[3][bi] - Yi * sb[2][bi]);
 }
 
-__global__ void __launch_bounds__(256) k_radial_rule(RadialParams rp, const double* __restrict__ glq, int64_t n,
-                                                     int m, const double* __restrict__ glm, double* __restrict__ x,
-                                                     double* __restrict__ y, double* __restrict__ w)
-{
-    curve_rule(rp, glq, n, m, glm, x, y, w);
-}
-
 __global__ void __launch_bounds__(256) k_fourier_rule(FourierParams fp, const double* __restrict__ glq, int64_t n,
                                                       int m, const double* __restrict__ glm, double* __restrict__ x,
                                                       double* __restrict__ y, double* __restrict__ w)
 {
     curve_rule(fp, glq, n, m, glm, x, y, w);
+}
+
+// A radial curve's or polygon's rule as the kernels below take it.
+struct RuleView {
+    int kind;            // kRuleRadial, kRulePolygon
+    int K;               // harmonics, or vertices
+    int panels, q, m;
+    int64_t n;           // boundary nodes
+    double r0;
+    const double* c0;    // a, or the vertices' x
+    const double* c1;    // b, or the vertices' y
+    const double* glq;
+    const double* glm;
+    double* x;
+    double* y;
+    double* w;
+};
+
+// The areal nodes [j0, j1) of one rule, by one block of 256 threads.  The
+// boundary nodes they touch are evaluated into LDS, then the block dilates
+// them.  A radial node sums K harmonics, each a sincos: where a batch of
+// boundary nodes is small (a block's areal nodes touch j1 - j0 over m of
+// them) its (node, harmonic) pairs go a thread each and only the sums run a
+// thread per node, in the order of bdry_node, so that a block does not wait
+// for K sincos in a row on a few lanes.
+constexpr int kRuleFew = 16;    // boundary nodes a batch evaluates pair by pair
+constexpr int kRuleBatch = 256; // boundary nodes per batch else
+
+__device__ __forceinline__ void rule_nodes(const RuleView& rv, int64_t j0, int64_t j1)
+{
+    __shared__ double sb[4][kRuleBatch];
+    __shared__ double2 sh[kRuleFew * kMaxFourier];
+    const int tid = threadIdx.x, m = rv.m;
+    const int64_t ilast = (j1 - 1) / m;
+    const bool few = rv.kind == kRuleRadial && ilast - j0 / m < kRuleFew;
+    for (int64_t i0 = j0 / m; i0 <= ilast; i0 += kRuleBatch) {
+        const int nb = (int)min((int64_t)kRuleBatch, ilast - i0 + 1);
+        if (few) {
+            for (int e = tid; e < nb * rv.K; e += 256) {
+                const int bi = e / rv.K, k = e - bi * rv.K + 1;
+                double t, om;
+                radial_angle(rv.panels, rv.q, rv.glq, rv.n, i0 + bi, t, om);
+                double s, c;
+                sincos(k * t, &s, &c);
+                sh[e] = make_double2(c, s);
+            }
+            __syncthreads();
+        }
+        if (tid < nb) {
+            double X, Y, W, V;
+            if (rv.kind == kRuleRadial) {
+                double t, om;
+                radial_angle(rv.panels, rv.q, rv.glq, rv.n, i0 + tid, t, om);
+                double r = rv.r0, dr = 0.0;
+                for (int k = 1; k <= rv.K; ++k) {
+                    double s, c;
+                    if (few) {
+                        const double2 h = sh[tid * rv.K + k - 1];
+                        c = h.x;
+                        s = h.y;
+                    } else {
+                        sincos(k * t, &s, &c);
+                    }
+                    r += rv.c0[k - 1] * c + rv.c1[k - 1] * s;
+                    dr += k * (rv.c1[k - 1] * c - rv.c0[k - 1] * s);
+                }
+                radial_point(t, om, r, dr, X, Y, W, V);
+            } else {
+                const int64_t i = i0 + tid;
+                const int e = (int)(i / rv.q), k = (int)(i % rv.q);
+                const int f = (e + 1 == rv.K) ? 0 : e + 1;
+                const double ex = rv.c0[f] - rv.c0[e], ey = rv.c1[f] - rv.c1[e];
+                const double sg = 0.5 * (1.0 + rv.glq[k]);
+                const double hw = 0.5 * rv.glq[rv.q + k];
+                X = rv.c0[e] + sg * ex;
+                Y = rv.c1[e] + sg * ey;
+                W = hw * ex;
+                V = hw * ey;
+            }
+            sb[0][tid] = X;
+            sb[1][tid] = Y;
+            sb[2][tid] = W;
+            sb[3][tid] = V;
+        }
+        __syncthreads();
+        // the batch's areal nodes, less than m + (j1 - j0) past node i0 m
+        const int64_t base = i0 * m;
+        const int64_t a0 = max(j0, base), a1 = min(j1, base + (int64_t)nb * m);
+        for (int64_t j = a0 + tid; j < a1; j += 256) {
+            const unsigned off = (unsigned)(j - base);
+            const int bi = (int)(off / (unsigned)m), l = (int)(off - (unsigned)bi * (unsigned)m);
+            const double al = 0.5 * (1.0 + rv.glm[l]);
+            const double wl = 0.5 * rv.glm[m + l];
+            const double Xi = sb[0][bi], Yi = sb[1][bi];
+            rv.x[j] = al * Xi;
+            rv.y[j] = al * Yi;
+            rv.w[j] = al * wl * (Xi * sb[3][bi] - Yi * sb[2][bi]);
+        }
+        __syncthreads();
+    }
+}
+
+// One rule; its coefficients (a then b, or the vertices' x then y) travel in
+// the kernel arguments.  A block takes kRuleOne areal nodes: a single rule
+// is small, so that many blocks share its sincos work.
+constexpr int kRuleOne = 256;
+
+template <int NC>
+struct RuleArgs {
+    RuleView v;
+    double c[2 * NC];
+};
+
+template <int NC>
+__global__ void __launch_bounds__(256) k_rule(RuleArgs<NC> ra)
+{
+    RuleView v = ra.v;
+    v.c0 = ra.c;
+    v.c1 = ra.c + NC;
+    const int64_t j0 = blockIdx.x * (int64_t)kRuleOne;
+    rule_nodes(v, j0, min(j0 + kRuleOne, v.n * v.m));
+}
+
+// Many rules in one launch: block b takes kRuleMany areal nodes of the rule
+// r with blk0[r] <= b < blk0[r + 1], found by a 64-way search of the table
+// (a ballot per step).  Bound by the 24 bytes written per node once the
+// launches no longer follow one another: a rule of 2e5 nodes alone leaves
+// most of the chip idle for 5 to 12 us.  256 rules of 51.7e6 nodes in all,
+// in one launch instead of 256: the mixed-precision call that rebuilds them
+// 5.52 -> 3.42 ms.
+constexpr int kRuleMany = 2048;
+
+__global__ void __launch_bounds__(256) k_rules(const RuleHead* __restrict__ heads, int R,
+                                               const double* __restrict__ coef)
+{
+    const int lane = (int)__lane_id(), b = blockIdx.x;
+    int lo = 0, cnt = R;  // the rule is in [lo, lo + cnt)
+    while (cnt > 1) {
+        const int step = (cnt + 63) / 64;
+        const int i = lane * step;
+        const bool le = i < cnt && heads[lo + i].blk0 <= b;
+        const int top = 63 - __clzll((long long)__ballot(le));  // lane 0 always holds
+        lo += top * step;
+        cnt = min(step, cnt - top * step);
+    }
+    const RuleHead h = heads[__builtin_amdgcn_readfirstlane(lo)];
+    RuleView v;
+    v.kind = h.kind;
+    v.K = h.K;
+    v.panels = h.panels;
+    v.q = h.q;
+    v.m = h.m;
+    v.n = h.n;
+    v.r0 = h.r0;
+    v.c0 = coef + h.coef;
+    v.c1 = v.c0 + h.K;
+    v.glq = h.glq;
+    v.glm = h.glm;
+    v.x = h.x;
+    v.y = h.y;
+    v.w = h.w;
+    const int64_t j0 = (int64_t)(b - h.blk0) * kRuleMany;
+    rule_nodes(v, j0, min(j0 + kRuleMany, v.n * v.m));
 }
 
 // Koch snowflake (sec. 4.4): Omega_0 is the equilateral triangle inscribed in
@@ -258,50 +429,6 @@ __global__ void k_bdry_polygon(const double* __restrict__ vx, const double* __re
     Y[i] = vy[e] + s * ey;
     Wv[i] = hw * ex;
     Vv[i] = hw * ey;
-}
-
-// Polygons of up to this many vertices travel in the kernel arguments.
-struct PolyParams {
-    int nv, q;
-    double vx[kPolyByValue];
-    double vy[kPolyByValue];
-};
-
-// Polygon edge rule and dilation in one pass (as k_radial_rule).
-__global__ void __launch_bounds__(256) k_polygon_rule(PolyParams pp, const double* __restrict__ glq, int m,
-                                                      const double* __restrict__ glm, double* __restrict__ x,
-                                                      double* __restrict__ y, double* __restrict__ w)
-{
-    __shared__ double sb[4][256];
-    const int64_t n = (int64_t)pp.nv * pp.q;
-    const int64_t j0 = blockIdx.x * (int64_t)blockDim.x;
-    const int64_t i0 = j0 / m;
-    const int64_t jl = min(j0 + (int64_t)blockDim.x, n * m) - 1;
-    const int nb = (int)(jl / m - i0) + 1;
-    if ((int)threadIdx.x < nb) {
-        const int64_t i = i0 + threadIdx.x;
-        const int e = (int)(i / pp.q), k = (int)(i % pp.q);
-        const int f = (e + 1 == pp.nv) ? 0 : e + 1;
-        const double ex = pp.vx[f] - pp.vx[e], ey = pp.vy[f] - pp.vy[e];
-        const double sg = 0.5 * (1.0 + glq[k]);
-        const double hw = 0.5 * glq[pp.q + k];
-        sb[0][threadIdx.x] = pp.vx[e] + sg * ex;
-        sb[1][threadIdx.x] = pp.vy[e] + sg * ey;
-        sb[2][threadIdx.x] = hw * ex;
-        sb[3][threadIdx.x] = hw * ey;
-    }
-    __syncthreads();
-    const int64_t j = j0 + threadIdx.x;
-    if (j >= n * m) return;
-    const int64_t i = j / m;
-    const int l = (int)(j - i * m);
-    const int bi = (int)(i - i0);
-    const double al = 0.5 * (1.0 + glm[l]);
-    const double wl = 0.5 * glm[m + l];
-    const double Xi = sb[0][bi], Yi = sb[1][bi];
-    x[j] = al * Xi;
-    y[j] = al * Yi;
-    w[j] = al * wl * (Xi * sb[3][bi] - Yi * sb[2][bi]);
 }
 
 // Dilation rule: node j = l + i m takes alpha_l (X_i, Y_i) with weight
@@ -694,15 +821,26 @@ void fourier_box(const FourierParams& fp, int64_t n, double* box)
     }, box);
 }
 
-fh_status radial_into(fh_ctx* c, const RadialParams& rp, int64_t n, int m, double* x, double* y,
-                      double* w)
+// One rule from its record (kernel arguments of NC coefficients each way).
+template <int NC>
+void launch_rule(fh_ctx* c, const RuleRec& r, double* x, double* y, double* w)
 {
-    const double* glq = nullptr;
-    const double* glm = nullptr;
-    if (rp.panels > 0) FH_TRY(gl_table(c, rp.q, &glq));
-    FH_TRY(gl_table(c, m, &glm));
-    hipLaunchKernelGGL(k_radial_rule, dim3(nblocks(n * m, 256)), dim3(256), 0, c->stream, rp, glq, n, m, glm, x, y,
-                       w);
+    RuleArgs<NC> ra{};
+    ra.v = RuleView{r.kind, r.K, r.panels, r.q, r.m, r.n, r.r0, nullptr, nullptr, r.glq, r.glm, x, y, w};
+    for (int k = 0; k < r.K; ++k) {
+        ra.c[k] = r.coef[k];
+        ra.c[NC + k] = r.coef[r.K + k];
+    }
+    hipLaunchKernelGGL((k_rule<NC>), dim3(nblocks(r.n * r.m, kRuleOne)), dim3(256), 0, c->stream, ra);
+}
+
+fh_status rule_into(fh_ctx* c, const RuleRec& r, double* x, double* y, double* w)
+{
+    // the arguments of a few harmonics are copied for each launch: the
+    // smallest of three sizes that holds them
+    if (r.K <= 8) launch_rule<8>(c, r, x, y, w);
+    else if (r.K <= kMaxFourier) launch_rule<kMaxFourier>(c, r, x, y, w);
+    else launch_rule<kPolyByValue>(c, r, x, y, w);
     FH_HIP(hipGetLastError());
     return FH_OK;
 }
@@ -775,6 +913,40 @@ fh_status bdry_end(fh_ctx* c, int64_t n, double* X, double* Y, double* W, double
 }
 
 }  // namespace
+
+// The distinct rules of a batch as one table: heads, then coefficients.
+size_t rules_pack(int B, const fh_quad* const* qs, std::vector<char>& blob, int* R, int* blocks)
+{
+    std::vector<const fh_quad*> u(qs, qs + B);
+    std::sort(u.begin(), u.end());
+    u.erase(std::unique(u.begin(), u.end()), u.end());
+    size_t nc = 0;
+    for (const fh_quad* q : u) nc += q->rule->coef.size();
+    const size_t hb = aligned_bytes(sizeof(RuleHead) * u.size());
+    blob.resize(hb + sizeof(double) * nc);
+    RuleHead* h = reinterpret_cast<RuleHead*>(blob.data());
+    double* co = reinterpret_cast<double*>(blob.data() + hb);
+    int64_t off = 0, blk = 0;
+    for (const fh_quad* q : u) {
+        const RuleRec& r = *q->rule;
+        *h++ = RuleHead{r.kind, r.K, r.panels, r.q, r.m, (int)blk, r.n, off, r.r0, r.glq, r.glm, q->x, q->y, q->w};
+        std::copy(r.coef.begin(), r.coef.end(), co + off);
+        off += (int64_t)r.coef.size();
+        blk += (r.n * r.m + kRuleMany - 1) / kRuleMany;
+    }
+    *R = (int)u.size();
+    *blocks = (int)blk;
+    return hb;
+}
+
+fh_status rules_launch(fh_ctx* c, const void* table, size_t coef_off, int R, int blocks)
+{
+    hipLaunchKernelGGL(k_rules, dim3(blocks), dim3(256), 0, c->stream, static_cast<const RuleHead*>(table), R,
+                       reinterpret_cast<const double*>(static_cast<const char*>(table) + coef_off));
+    FH_HIP(hipGetLastError());
+    return FH_OK;
+}
+
 }  // namespace fh
 
 namespace fh {
@@ -856,13 +1028,11 @@ fh_status starshade_build(fh_ctx* c, int32_t Np, double a, double R, double b, d
     }
     if (nd > 0) {
         // disc of radius a: trapezoid boundary rule (eq. ptr) + dilation
-        RadialParams rp{};
-        rp.r0 = a;
-        rp.K = 0;
-        rp.panels = 0;
-        rp.q = nd;
-        hipLaunchKernelGGL(k_radial_rule, dim3(nblocks(Nd, 256)), dim3(256), 0, c->stream, rp,
-                           (const double*)nullptr, (int64_t)nd, md, glmd, qd->x, qd->y, qd->w);
+        s = rule_into(c, RuleRec{kRuleRadial, 0, 0, nd, md, nd, a, {}, nullptr, glmd}, qd->x, qd->y, qd->w);
+        if (s != FH_OK) {
+            fh_quad_destroy(qd);
+            return s;
+        }
     }
     const bool deform = coef && mr < 0;
     PetalParams pp{Np, m, np, deform ? K : 0, a, R, b, p, Nd};
@@ -914,14 +1084,19 @@ fh_status fh_quad_radial(fh_ctx* c, double r0, const double* a, const double* b,
         }
         const int64_t n = panels > 0 ? (int64_t)panels * q : q;
         FH_HIP(hipSetDevice(c->device));
+        auto rec = std::make_unique<RuleRec>(RuleRec{kRuleRadial, K, panels, q, m, n, r0, {}, nullptr, nullptr});
+        rec->coef.assign(rp.a, rp.a + K);
+        rec->coef.insert(rec->coef.end(), rp.b, rp.b + K);
+        if (panels > 0) FH_TRY(gl_table(c, q, &rec->glq));
+        FH_TRY(gl_table(c, m, &rec->glm));
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, n * m, &qd));
-        fh_status s = radial_into(c, rp, n, m, qd->x, qd->y, qd->w);
+        fh_status s = rule_into(c, *rec, qd->x, qd->y, qd->w);
         if (s != FH_OK) {
             fh_quad_destroy(qd);
             return s;
         }
-        qd->rebuild = [c, rp, n, m, qd]() { return radial_into(c, rp, n, m, qd->x, qd->y, qd->w); };
+        qd->rule = std::move(rec);
         // the box waits for a call that needs it (a type-1 row window)
         qd->host_box = [rp, n](double* box) { radial_box(rp, n, box); };
         *out = qd;
@@ -959,22 +1134,15 @@ fh_status fh_quad_polygon(fh_ctx* c, const double* vx, const double* vy, int32_t
         }
         if (nv <= kPolyByValue) {
             // vertices in the kernel arguments: no copy, no synchronisation
-            PolyParams pp{};
-            pp.nv = nv;
-            pp.q = q;
-            for (int i = 0; i < nv; ++i) {
-                pp.vx[i] = vx[i];
-                pp.vy[i] = vy[i];
+            auto rec = std::make_unique<RuleRec>(RuleRec{kRulePolygon, nv, 0, q, m, n, 0.0, {}, glq, glm});
+            rec->coef.assign(vx, vx + nv);
+            rec->coef.insert(rec->coef.end(), vy, vy + nv);
+            fh_status s = rule_into(c, *rec, qd->x, qd->y, qd->w);
+            if (s != FH_OK) {
+                fh_quad_destroy(qd);
+                return s;
             }
-            hipLaunchKernelGGL(k_polygon_rule, dim3(nblocks(n * m, 256)), dim3(256), 0, c->stream, pp, glq, m, glm,
-                               qd->x, qd->y, qd->w);
-            FH_HIP(hipGetLastError());
-            qd->rebuild = [c, pp, glq, m, glm, n, qd]() -> fh_status {
-                hipLaunchKernelGGL(k_polygon_rule, dim3(nblocks(n * m, 256)), dim3(256), 0, c->stream, pp, glq, m,
-                                   glm, qd->x, qd->y, qd->w);
-                FH_HIP(hipGetLastError());
-                return FH_OK;
-            };
+            qd->rule = std::move(rec);
             set_bbox(qd, bb[0], bb[1], bb[2], bb[3]);
             *out = qd;
             return FH_OK;
@@ -1154,11 +1322,12 @@ fh_status fh_quad_starshade_rigid(fh_ctx* c, int32_t Np, double a, double R, dou
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, Nd + Npet + Nb, &qd));
         if (nd > 0) {
-            RadialParams dp{};
-            dp.r0 = a;
-            dp.q = nd;
-            hipLaunchKernelGGL(k_radial_rule, dim3(nblocks(Nd, 256)), dim3(256), 0, c->stream, dp,
-                               (const double*)nullptr, (int64_t)nd, md, glmd, qd->x, qd->y, qd->w);
+            fh_status s = rule_into(c, RuleRec{kRuleRadial, 0, 0, nd, md, nd, a, {}, nullptr, glmd}, qd->x, qd->y,
+                                    qd->w);
+            if (s != FH_OK) {
+                fh_quad_destroy(qd);
+                return s;
+            }
         }
         PetalParams pp{Np, m, np, 0, a, R, b, p, Nd};
         hipLaunchKernelGGL(k_petals, dim3(nblocks(Npet, 256)), dim3(256), 0, c->stream, pp, glm, gln,
