@@ -520,11 +520,11 @@ def grad_ratio(fh, precision, steps, warmup):
 
 
 # FP64 flops per node-target pair of the edge-integral kernel (an FMA counts
-# 2): the inner loop of k_nsli as built, per pair 31 FMAs and 9 adds or
-# multiplies (displacement, r^2, cross product, turns and their reduction,
-# the two Taylor series of sin/cos(pi f), the refined reciprocal of r^2 and
-# the three accumulations).
-NSLI_FLOPS_PER_PAIR = 71
+# 2): the inner loop of k_nsli, per pair 24 FMAs and 9 adds or multiplies
+# (displacement, r^2, cross product, turns and their reduction, the two
+# polynomials of sin/cos(pi f), the refined reciprocal of r^2 and the two
+# accumulations).
+NSLI_FLOPS_PER_PAIR = 57
 
 
 def nsli_throughput(fh, wl, steps, warmup, cpu_seconds):
