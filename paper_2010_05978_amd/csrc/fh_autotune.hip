@@ -45,7 +45,7 @@ std::string batch_key(const fh_ctx* c, int B, int n1, int n2, int64_t Ntot, int6
     return buf;
 }
 
-bool cache_lookup(const char* path, const std::string& key, fh_options* o)
+bool cache_lookup(const char* path, const std::string& key, fh_options* o, bool* automatic)
 {
     if (!path) return false;
     std::ifstream f(path);
@@ -61,12 +61,13 @@ bool cache_lookup(const char* path, const std::string& key, fh_options* o)
                               &t.sigma, &t.tile, &t.max_subproblem, &t.spread_method) != 4)
             continue;
         *o = t;  // the last matching line wins
+        *automatic = line.find("\"automatic\": 1") != std::string::npos;
         found = true;
     }
     return found;
 }
 
-void cache_append(const char* path, const std::string& key, const fh_options& o, double ms)
+void cache_append(const char* path, const std::string& key, const fh_options& o, double ms, bool automatic)
 {
     if (!path) return;
     std::ofstream f(path, std::ios::app);
@@ -74,8 +75,8 @@ void cache_append(const char* path, const std::string& key, const fh_options& o,
     char buf[400];
     snprintf(buf, sizeof(buf),
              "{\"key\": \"%s\", \"sigma\": %.2f, \"tile\": %d, \"max_subproblem\": %d, \"spread_method\": %d, "
-             "\"ms\": %.5f}\n",
-             key.c_str(), o.sigma, o.tile, o.max_subproblem, o.spread_method, ms);
+             "\"ms\": %.5f, \"automatic\": %d}\n",
+             key.c_str(), o.sigma, o.tile, o.max_subproblem, o.spread_method, ms, automatic ? 1 : 0);
     f << buf;
 }
 
@@ -111,8 +112,10 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
                fh_options* best, Call call)
 {
     fh_options hit{};
-    if (cache_lookup(cache_path, key, &hit)) {
+    bool automatic = false;
+    if (cache_lookup(cache_path, key, &hit, &automatic)) {
         c->opt = merged(c->opt, hit);
+        c->tuned_auto = automatic;
         *best = c->opt;
         return FH_OK;
     }
@@ -122,6 +125,8 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
     FH_HIP(hipEventCreate(&e1));
     const bool timing = c->timing;
     c->timing = false;
+    const bool saved_auto = c->tuned_auto;
+    c->tuned_auto = false;
     double best_ms = 1e300;
     fh_options best_o = saved;
     fh_status st = FH_OK;
@@ -170,16 +175,32 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
                         best_o = o;
                     }
                 }
+    // the automatic choice, which may take a path that no option names
+    if (st == FH_OK && best_ms < 1e300) {
+        c->opt = merged(saved, fh_options{});
+        fh_status s = FH_OK;
+        for (int w = 0; w < 2 && s == FH_OK; ++w) s = call();
+        FH_HIP(hipEventRecord(e0, c->stream));
+        for (int r = 0; r < reps && s == FH_OK; ++r) s = call();
+        FH_HIP(hipEventRecord(e1, c->stream));
+        FH_HIP(hipEventSynchronize(e1));
+        float ms = 0;
+        FH_HIP(hipEventElapsedTime(&ms, e0, e1));
+        automatic = s == FH_OK && ms / reps < best_ms;
+        if (s != FH_OK) st = s;
+    }
     c->timing = timing;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st != FH_OK) {
         c->opt = saved;
+        c->tuned_auto = saved_auto;
         return st;
     }
     c->opt = best_o;
     *best = best_o;
-    cache_append(cache_path, key, best_o, best_ms);
+    c->tuned_auto = automatic;
+    cache_append(cache_path, key, best_o, best_ms, automatic);
     return FH_OK;
 }
 

@@ -124,6 +124,7 @@ struct InstParams {
     double pa, px, py, pc;
     double cx, cy, s1, s2;
     const double* src;
+    int32_t sh1;       // first fine-grid column of the window (k_win_spread)
 };
 
 // Tiles need not divide the grid: the last tile of a row (of a column)
@@ -221,6 +222,11 @@ struct fh_ctx {
     std::map<std::tuple<int, long long, long long>, fh::InvPhiCheb> cheb_cache;
     std::map<std::tuple<int, long long, int>, void*> poly_cache;  // (w, beta bits, precision)
     std::map<std::pair<int, int>, void*> lds_tw_cache;             // (LDS FFT length, real size)
+    std::map<int, void*> roots_cache;  // roots of unity by order (roots_table)
+    // The autotuner found the automatic choice of path faster than every
+    // spread method with its options (fh_autotune_*): where the window path
+    // serves, it is taken although the options name a method.
+    bool tuned_auto = false;
     std::map<void*, size_t> owned;  // every hipMalloc'd block and its size
     double* bbox_dev = nullptr;      // bounding-box reduction scratch
     double* bbox_host = nullptr;     // pinned readback of the box
@@ -287,6 +293,9 @@ struct fh_quad {
     double D = 0.0;
     bool bbox_valid = false;
     double bbox[4] = {0, 0, 0, 0};  // xmin, xmax, ymin, ymax
+    // The nodes are the caller's own, in no order that is known (a generated
+    // rule's follow rays or arcs).
+    bool user_nodes = false;
     // The boundary parameters of a rule built by one launch with its
     // parameters by value (radial curves and small polygons), from which a
     // batched call rebuilds it in place; null for the others.
@@ -343,6 +352,9 @@ fh_status device_bbox2(fh_ctx* c, const double* x1, const double* y1, int64_t n1
                        const double* y2, int64_t n2, double* bb2);
 void timing_mark(fh_ctx* c, int i);
 void timing_finish(fh_ctx* c);
+
+// Device table of the nf roots exp(-2 pi i m/nf), m < nf (complex double).
+fh_status roots_table(fh_ctx* c, int nf, const double2** dev);
 
 // kernel launchers shared across translation units (fh_field.hip)
 fh_status launch_zero(fh_ctx* c, void* p, size_t bytes);

@@ -396,6 +396,32 @@ fh_status iphi_table(fh_ctx* c, const EsKernel& k, int n, int nf, const double**
     return FH_OK;
 }
 
+fh_status roots_table(fh_ctx* c, int nf, const double2** dev)
+{
+    auto it = c->roots_cache.find(nf);
+    if (it != c->roots_cache.end()) {
+        *dev = static_cast<const double2*>(it->second);
+        return FH_OK;
+    }
+    const long double two_pi = 6.283185307179586476925286766559005768L;
+    std::vector<double2> h(nf);
+    for (int m = 0; m < nf; ++m) {
+        const long double a = two_pi * (long double)m / (long double)nf;
+        h[m] = make_double2((double)cosl(a), (double)-sinl(a));
+    }
+    void* p = nullptr;
+    FH_TRY(dev_alloc(c, sizeof(double2) * (size_t)nf, &p));
+    if (hipMemcpy(p, h.data(), sizeof(double2) * (size_t)nf, hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)dev_free(c, p);
+        set_error("copying the roots of unity to the device failed");
+        return FH_ERR_HIP;
+    }
+    c->roots_cache[nf] = p;
+    *dev = static_cast<const double2*>(p);
+    return FH_OK;
+}
+
 // Chebyshev interpolant of f(s) = 1/Phi(theta_max sqrt((s+1)/2)), s in
 // [-1,1], at the Chebyshev points of the first kind; the degree doubles
 // until the interpolant matches direct evaluation to ~1e-14 relative.
@@ -747,6 +773,7 @@ fh_status fh_set_options(fh_ctx* c, const fh_options* opt)
     FH_ARG(c, FH_ERR_INVALID_ARG, "ctx is NULL");
     FH_TRY(check_options(opt));
     c->opt = opt ? *opt : fh_options{};
+    c->tuned_auto = false;
     return FH_OK;
 }
 

@@ -29,6 +29,7 @@
 // rocFFT transforms the stored rows, and a transpose pads the needed columns
 // back to full length for a second rocFFT pass.
 #include "fh_kernels.hpp"
+#include "fh_window.hpp"
 
 #include <hipcub/device/device_radix_sort.hpp>
 
@@ -193,6 +194,143 @@ fh_status launch_t1_rows(fh_ctx* c, const LdsCols& lr, int reach, int B, int gro
     return FH_OK;
 }
 
+// Cells that the nodes of [lo, hi] (rule units) reach along one axis: first
+// cell and count, as window_rows; false when they do not fit the period or
+// the integers.
+bool reach_cells(double lo, double hi, double s, int W, int nf, int& first, int& span)
+{
+    const double a = std::floor(lo * s - 0.5 * W) - 1.0, b = std::ceil(hi * s - 0.5 * W) + W + 1.0;
+    if (!(std::fabs(a) < 1e9 && b - a < nf)) return false;
+    first = (int)a;
+    span = (int)(b - a);
+    return true;
+}
+
+// Whether the window path (fh_window.hpp) takes the call, and its geometry.
+// Its window or windows must fit a workgroup's 64 KB of LDS with the staging,
+// which bounds it at some 47 x 47 cells in FP64 and 39 x 39 in FP32 (more
+// where it is narrow): few enough rows that the dense sums cost less than transforms
+// padded with zeros (8 flops per row and output; 2048 x 2048 outputs from 27
+// rows, FP64: 35 us against 122).  The matrix-core
+// spread needs the polynomial table and a kernel of at most 16 cells, and a
+// rule in its generator's order (any order is right, but sixteen consecutive
+// nodes far apart cost sixteen times the products).  Options that name a
+// spread, a tile or an item size keep the tiled path, as does the
+// deterministic one, whose batches promise to run as they did.
+template <class R>
+bool window_plan(fh_ctx* c, const T1Plan& pl, int B, const fh_quad* const* qs, std::vector<InstParams>& inst,
+                 int64_t Ntot, WinGeom& wg, fh_status& st)
+{
+    st = FH_OK;
+    const fh_options& o = c->opt;
+    const bool automatic = o.spread_method == 0 && o.tile == 0 && o.max_subproblem == 0;
+    if (!(automatic || c->tuned_auto) || o.deterministic || pl.k.w > 16 || !pl.k.poly || B > 65535) return false;
+    int SX = 16, SY = 16;
+    for (int b = 0; b < B; ++b) {
+        if (qs[b]->user_nodes || qs[b]->N == 0) return false;
+        double bb[4];
+        st = quad_bbox(c, qs[b], bb);
+        if (st != FH_OK) return false;
+        int l1, l2, s1, s2;
+        if (!reach_cells(bb[0], bb[1], inst[b].s1, pl.k.w, pl.gg.nf1, l1, s1) ||
+            !reach_cells(bb[2], bb[3], inst[b].s2, pl.k.w, pl.gg.nf2, l2, s2))
+            return false;
+        inst[b].sh1 = l1;
+        inst[b].sh2 = l2;
+        SX = std::max(SX, s1);
+        SY = std::max(SY, s2);
+        // (an early end for the common large windows)
+        if (SY > 64 || win_lds(SX, SY, pl.k.w, sizeof(R)) > kLdsBudget) return false;
+    }
+    if (SX > pl.gg.nf1 || SY > pl.gg.nf2 || SX > 65535) return false;
+    wg.nf1 = pl.gg.nf1;
+    wg.nf2 = pl.gg.nf2;
+    wg.SX = SX;
+    wg.SY = SY;
+    if (win_dft_lds(SX, (SY + 15) / 16, 16, sizeof(R)) > kLdsBudget) return false;
+    // workgroups: as many as are resident at once, at least two batches of
+    // 64 nodes per wavefront
+    const int64_t per_cu = std::min<int64_t>(3, kCuLds / (win_lds(SX, SY, pl.k.w, sizeof(R))));
+    const int64_t resident = std::max<int64_t>(1, c->cu_count * per_cu / B);
+    const int64_t enough = (Ntot / B + 128 * kWinWaves - 1) / (128 * kWinWaves);
+    wg.nblk = (int)std::max<int64_t>(1, std::min(resident, enough));
+    return true;
+}
+
+// The type-1 call through the window path (see fh_window.hpp): spread, sum,
+// transform.
+template <class R>
+fh_status t1_window(fh_ctx* c, const T1Plan& pl, const WinGeom& wg, int B, const std::vector<InstParams>& inst,
+                    std::vector<EpiInst>& epi, int n1, int n2, double h1, double h2, double xc, double yc, R* u,
+                    size_t extra_bytes, void** extra)
+{
+    using C2 = typename V2<R>::T;
+    const int cells = wg.SX * wg.SY, MT = (wg.SY + 15) / 16, W = pl.k.w;
+    for (int b = 0; b < B; ++b) {
+        epi[b].sh1 = inst[b].sh1;
+        epi[b].sh2 = inst[b].sh2;
+    }
+    const double *ip1 = nullptr, *ip2 = nullptr;
+    const double2 *r1 = nullptr, *r2 = nullptr;
+    FH_TRY(iphi_table(c, pl.k, n1, wg.nf1, &ip1));
+    FH_TRY(iphi_table(c, pl.k, n2, wg.nf2, &ip2));
+    FH_TRY(roots_table(c, wg.nf1, &r1));
+    FH_TRY(roots_table(c, wg.nf2, &r2));
+    const size_t nwin = (size_t)B * wg.nblk;
+    FH_TRY(arena_reserve(c, aligned_bytes(sizeof(C2) * nwin * cells) + aligned_bytes(sizeof(C2) * (size_t)B * cells) +
+                                aligned_bytes(sizeof(InstParams) * B) + aligned_bytes(sizeof(EpiInst) * B) +
+                                aligned_bytes(extra_bytes)));
+    C2* part = c->arena.take<C2>(nwin * cells);
+    C2* G = c->arena.take<C2>((size_t)B * cells);
+    InstParams* dinst = c->arena.take<InstParams>(B);
+    EpiInst* depi = c->arena.take<EpiInst>(B);
+    if (extra) *extra = c->arena.take<char>(extra_bytes);
+    if (!u) u = static_cast<R*>(*extra);
+    if (B > 1) {
+        FH_HIP(hipMemcpyAsync(dinst, inst.data(), sizeof(InstParams) * B, hipMemcpyHostToDevice, c->stream));
+        FH_HIP(hipMemcpyAsync(depi, epi.data(), sizeof(EpiInst) * B, hipMemcpyHostToDevice, c->stream));
+    }
+    const InstParams* tab = B > 1 ? dinst : nullptr;
+    const EpiInst* etab = B > 1 ? depi : nullptr;
+    timing_mark(c, 0);
+    timing_mark(c, 1);
+    const size_t slds = win_lds(wg.SX, wg.SY, W, sizeof(R));
+    const dim3 sgrid(wg.nblk, B);
+    switch (W) {
+#define FH_WIN_CASE(w)                                                                                           case w:                                                                                                          hipLaunchKernelGGL((k_win_spread<R, w>), sgrid, dim3(64 * kWinWaves), slds, c->stream, inst[0], tab,                            wg, part, (const R*)pl.k.poly);                                                           break;
+        FH_WIN_CASE(2) FH_WIN_CASE(3) FH_WIN_CASE(4) FH_WIN_CASE(5) FH_WIN_CASE(6) FH_WIN_CASE(7) FH_WIN_CASE(8)
+        FH_WIN_CASE(9) FH_WIN_CASE(10) FH_WIN_CASE(11) FH_WIN_CASE(12) FH_WIN_CASE(13) FH_WIN_CASE(14)
+        FH_WIN_CASE(15) FH_WIN_CASE(16)
+#undef FH_WIN_CASE
+    default: set_error("kernel width %d unsupported", W); return FH_ERR_UNSUPPORTED;
+    }
+    timing_mark(c, 2);
+    hipLaunchKernelGGL((k_win_sum<R>), dim3(nblocks(cells, 16), B), dim3(256), 0, c->stream, (const C2*)part, cells,
+                       wg.nblk, G);
+    timing_mark(c, 3);
+    // output rows per workgroup: up to 128, fewer while that leaves fewer
+    // than two workgroups per CU (each repeats the columns' sum, which costs
+    // as much as SX rows)
+    const int64_t cols = (n1 + 63) / 64;
+    int KC = 128;
+    while (KC > 16 && cols * ((n2 + KC - 1) / KC) * B < 2 * (int64_t)c->cu_count) KC /= 2;
+    const EpiParams ep{n1, n2, wg.nf1, wg.nf2, h1, h2, xc, yc, ip1, ip2};
+    const dim3 dgrid((unsigned)cols, (n2 + KC - 1) / KC, B);
+    const size_t dlds = win_dft_lds(wg.SX, MT, KC, sizeof(R));
+#define FH_WIN_DFT(mt)                                                                                            hipLaunchKernelGGL((k_win_dft<R, mt>), dgrid, dim3(256), dlds, c->stream, (const C2*)G, wg, u, ep, epi[0],                        etab, r1, r2, KC)
+    switch (MT) {
+    case 1: FH_WIN_DFT(1); break;
+    case 2: FH_WIN_DFT(2); break;
+    case 3: FH_WIN_DFT(3); break;
+    default: FH_WIN_DFT(4); break;
+    }
+#undef FH_WIN_DFT
+    FH_HIP(hipGetLastError());
+    timing_mark(c, 4);
+    timing_mark(c, 5);
+    return FH_OK;
+}
+
 // The type-1 pipeline for B instances sharing one grid geometry; u is device
 // memory (B x n2 x n1).  With `capture`, the launch sequence is recorded into
 // a hipGraph keyed by everything baked into it and replayed.  With
@@ -233,6 +371,14 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     }
     FH_ARG(Ntot < ((int64_t)1 << 31), FH_ERR_UNSUPPORTED, "%lld nodes in one call; at most 2^31 - 1",
            (long long)Ntot);
+    if (!rebuild) {
+        std::vector<InstParams> winst(inst);
+        WinGeom wg;
+        fh_status ws;
+        if (window_plan<R>(c, pl, B, qs, winst, Ntot, wg, ws))
+            return t1_window<R>(c, pl, wg, B, winst, epi, n1, n2, h1, h2, xc, yc, u, extra_bytes, extra);
+        FH_TRY(ws);
+    }
     size_items(c, gg, Ntot);
     // hold only the reachable rows unless they cover most of the period
     const int rows = (max_span + gg.T - 1) / gg.T * gg.T;

@@ -1048,6 +1048,46 @@ __host__ __device__ inline size_t mfma_wave_lds(int NB, int T, int MS, size_t rs
     return (3 * (size_t)mfma_rows(NB, T, MS) + 4 * (size_t)MS) * rsize + 2 * (size_t)MS * sizeof(int);
 }
 
+// Kernel values of MS staged points by the mirrored pairs (lane (pg, pp) as in
+// k_spread_mfma): arguments 0..MS-1 are the points' x, whose values go to the
+// first operand array, the next MS their y, whose values times the strength
+// go to the second and third.
+template <class R, int W, int MS>
+__device__ __forceinline__ void mfma_stage_values(R* rows, const R* ttab, const R* ctab, const R* ce, const R* co,
+                                                  int pg, int pp, int P, int T, int AL)
+{
+    constexpr int NPAIR = poly_npair(W), NE = poly_ne(W), NO = poly_no(W);
+    constexpr int KGP = 64 / NPAIR;
+#pragma unroll
+    for (int r = 0; r < (2 * MS + KGP - 1) / KGP; ++r) {
+        const int qq = r * KGP + pg;
+        if (pg < KGP && qq < 2 * MS) {
+            const R t = ttab[qq], s2 = t * t;
+            R e = ce[0], o = co[0];
+#pragma unroll
+            for (int j = 1; j < NE; ++j) e = e * s2 + ce[j];
+#pragma unroll
+            for (int j = 1; j < NO; ++j) o = o * s2 + co[j];
+            const R lo = e + t * o, hi = e - t * o;  // cells pp and W - 1 - pp
+            const bool two = 2 * pp != W - 1;
+            const int q = qq < MS ? qq : qq - MS;
+            R* row = rows + q * P + T - 1;
+            if (qq < MS) {
+                row[pp] = lo;
+                if (two) row[W - 1 - pp] = hi;
+            } else {
+                const R cr = ctab[2 * q], ci = ctab[2 * q + 1];
+                row[AL + pp] = cr * lo;
+                row[2 * AL + pp] = ci * lo;
+                if (two) {
+                    row[AL + W - 1 - pp] = cr * hi;
+                    row[2 * AL + W - 1 - pp] = ci * hi;
+                }
+            }
+        }
+    }
+}
+
 // The register allocator is asked for eight waves per SIMD in FP32 (61
 // registers; seven by default: batch spread 0.93 -> 0.88 ms) and four in
 // FP64, where the mirrored-pair evaluation would otherwise take 130
@@ -1067,7 +1107,6 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
     constexpr int NP = poly_np(W);  // coefficients per kernel polynomial
     constexpr int KG = 64 / W;          // lane groups evaluating kernel values (no table)
     constexpr int NPAIR = poly_npair(W), NE = poly_ne(W), NO = poly_no(W);
-    constexpr int KGP = 64 / NPAIR;     // lane groups evaluating mirrored pairs (table)
     static_assert(W <= 16 * NB, "the padded tile must fit the blocks");
     static_assert(MS % 16 == 0 && MS <= 64, "points are staged in sixteens, one per lane at most");
     extern __shared__ unsigned char smem_raw[];
@@ -1138,34 +1177,7 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
             // the kernel values: arguments 0..MS-1 are the points' x, the
             // next MS their y (times the strength)
             if (has_poly) {
-#pragma unroll
-                for (int r = 0; r < (2 * MS + KGP - 1) / KGP; ++r) {
-                    const int qq = r * KGP + pg;
-                    if (pg < KGP && qq < 2 * MS) {
-                        const R t = ttab[qq], s2 = t * t;
-                        R e = ce[0], o = co[0];
-#pragma unroll
-                        for (int j = 1; j < NE; ++j) e = e * s2 + ce[j];
-#pragma unroll
-                        for (int j = 1; j < NO; ++j) o = o * s2 + co[j];
-                        const R lo = e + t * o, hi = e - t * o;  // cells pp and W - 1 - pp
-                        const bool two = 2 * pp != W - 1;
-                        const int q = qq < MS ? qq : qq - MS;
-                        R* row = rows + q * P + T - 1;
-                        if (qq < MS) {
-                            row[pp] = lo;
-                            if (two) row[W - 1 - pp] = hi;
-                        } else {
-                            const R cr = ctab[2 * q], ci = ctab[2 * q + 1];
-                            row[AL + pp] = cr * lo;
-                            row[2 * AL + pp] = ci * lo;
-                            if (two) {
-                                row[AL + W - 1 - pp] = cr * hi;
-                                row[2 * AL + W - 1 - pp] = ci * hi;
-                            }
-                        }
-                    }
-                }
+                mfma_stage_values<R, W, MS>(rows, ttab, ctab, ce, co, pg, pp, P, T, AL);
             } else {
 #pragma unroll
                 for (int r = 0; r < (2 * MS + KG - 1) / KG; ++r) {
@@ -1807,6 +1819,7 @@ struct EpiInst {
     int sh2;        // row shift of the instance's window
     int rows;       // rows held for the instance (its window)
     int roff;       // its first row in the band array
+    int sh1;        // column shift (k_win_dft)
 };
 
 struct EpiParams {

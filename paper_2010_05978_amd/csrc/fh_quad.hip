@@ -1371,6 +1371,7 @@ fh_status fh_quad_from_nodes(fh_ctx* c, const double* x, const double* y, const 
         FH_HIP(hipSetDevice(c->device));
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, N, &qd));
+        qd->user_nodes = true;
         if (N > 0) {
             hipMemcpyKind kind = mem == FH_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
             FH_HIP(hipMemcpyAsync(qd->x, x, sizeof(double) * N, kind, c->stream));

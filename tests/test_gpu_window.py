@@ -1,0 +1,125 @@
+"""Type 1 through the window path (rules that reach a few fine-grid cells):
+kernel widths, window sizes at their limits, ragged grids, orders of nodes,
+source terms, translated grids and batches, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fh():
+    import paper_2010_05978_amd as fh
+    return fh
+
+
+def cpu(t):
+    return t.detach().cpu().numpy()
+
+
+def check(u, rule, lam, z, grid, tol, occulter=False, src=None, D=0.0):
+    xi, eta = oracle.grid_targets(*grid)
+    ref = oracle.fresnel_direct_src(*rule, lam, z, xi, eta, src=src, D=D)
+    got = (1.0 - cpu(u) if occulter else cpu(u)).ravel()
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print(f"  window: relative L2 error {err:.1e} (tol {tol:.0e})", flush=True)
+    assert err <= tol
+
+
+# every kernel width that the matrix-core tile holds
+@pytest.mark.parametrize("prec,tol", [("fp64", 10.0 ** -k) for k in range(1, 14)] + [("mixed", 10.0 ** -k) for k in (2, 3, 4, 5)])
+def test_widths(fh, prec, tol):
+    ctx = fh.Context(prec, tol=tol)
+    a, b = [0.02, 0.0, 0.1], [0.0, 0.05, 0.0]
+    q = ctx.quad_radial(1.0, a, b, 6, 12, 15)
+    grid = (70, 50, 0.004, 0.005)
+    u = ctx.field_grid(q, 0.25, 1.0, *grid)
+    check(u, oracle.quad_radial(1.0, a, b, 6, 12, 15), 0.25, 1.0, grid, tol)
+    ctx.close()
+
+
+# windows from the smallest (padded to the 16-cell tile) to past the largest
+# (which falls back to the tiled path), square and narrow; ragged grids at the
+# edges of the 64-column and 16-row output tiles
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-9), ("mixed", 1e-5)])
+@pytest.mark.parametrize("h", [0.0002, 0.006, 0.0115, 0.0125, 0.019, 0.024, 0.04])
+@pytest.mark.parametrize("n1,n2", [(64, 64), (66, 130), (190, 18), (2, 250)])
+def test_window_sizes_and_ragged_grids(fh, prec, tol, h, n1, n2):
+    ctx = fh.Context(prec, tol=tol)
+    q = ctx.quad_radial(1.0, None, None, 5, 12, 20)
+    tiled = fh.Context(prec, tol=tol, options=fh.fh_options(sigma=0, kernel_width=0, beta=0.0, tile=0,
+                                                            max_subproblem=0, spread_method=2, deterministic=0))
+    # R^2/(lambda z) = 3.33: the field on the axis is not one of its zeros
+    # (at 4 it is, and 2.6e-9 of what is left is lost to cancellation on
+    # either path)
+    lam, z = 0.25, 1.2
+    rule = oracle.quad_radial(1.0, None, None, 5, 12, 20)
+    for grid in ((n1, n2, h, h), (n1, n2, h, 0.3 * h)):
+        print(f"window {prec} {grid}", flush=True)
+        u = ctx.field_grid(q, lam, z, *grid, occulter=True)
+        check(u, rule, lam, z, grid, tol, occulter=True)
+        # the general path sums the same kernel values: what is left is the
+        # rounding of sums of 1200 nodes and some 60 x 60 cells of size
+        # area/(lambda z) = 10, in either precision's epsilon
+        v = tiled.field_grid(q, lam, z, *grid, occulter=True)
+        assert float((u - v).abs().max()) <= 10.0 * 100.0 * (2.3e-16 if prec == "fp64" else 1.2e-7)
+    tiled.close()
+    ctx.close()
+
+
+# nodes in an order that keeps sixteen of them together, and in orders that do
+# not (two radii a ray; a snowflake's small triangles; a ray of 1 node)
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-9), ("mixed", 1e-5)])
+@pytest.mark.parametrize("rule", ["ray", "two", "one", "koch", "starshade"])
+def test_orders(fh, prec, tol, rule):
+    ctx = fh.Context(prec, tol=tol)
+    if rule == "koch":
+        q, ref = ctx.quad_koch(4, [9, 5, 3, 2, 2]), oracle.quad_koch(4, [9, 5, 3, 2, 2])
+    elif rule == "starshade":
+        args = (12, 0.5, 1.0, 0.4, 6.0, 20, 6, 80, 12)
+        q, ref = ctx.quad_starshade(*args), oracle.quad_starshade(*args)
+    else:
+        args = {"ray": (6, 12, 40), "two": (40, 12, 2), "one": (100, 13, 1)}[rule]
+        q, ref = ctx.quad_radial(1.0, None, None, *args), oracle.quad_radial(1.0, None, None, *args)
+    grid = (98, 102, 0.008, 0.007)
+    u = ctx.field_grid(q, 0.25, 1.0, *grid)
+    check(u, ref, 0.25, 1.0, grid, tol)
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-9), ("mixed", 1e-5)])
+def test_translated_lit_and_batched(fh, prec, tol):
+    ctx = fh.Context(prec, tol=tol)
+    grid = (130, 70, 0.006, 0.007, 0.21, -0.35)
+    shapes = [(1.0, [0.1], [0.0], 5, 12, 21), (0.7, None, None, 3, 16, 40), (1.1, [0.0, 0.05], [0.1, 0.0], 4, 11, 30)]
+    quads = [ctx.quad_radial(*s) for s in shapes]
+    refs = [oracle.quad_radial(*s) for s in shapes]
+    x, y, _ = refs[0]
+    src = (1.0 + 0.2 * np.cos(x)) * np.exp(0.5j * np.sin(2 * y))
+    quads[0].set_illumination(torch.tensor(src, device="cuda"), 7.0)
+    lams, zs, occ = np.array([0.25, 0.3, 0.28]), np.array([1.0, 1.1, 0.9]), np.array([0, 1, 0], dtype=np.int32)
+    for rep in range(2):
+        u = ctx.field_grid_batch(quads, lams, zs, *grid[:4], xc=grid[4], yc=grid[5], occulter=occ)
+        for b in range(3):
+            check(u[b], refs[b], lams[b], zs[b], grid, tol, bool(occ[b]), src if b == 0 else None, 7.0 if b == 0 else 0.0)
+    one = ctx.field_grid(quads[0], lams[0], zs[0], *grid[:4], xc=grid[4], yc=grid[5])
+    check(one, refs[0], lams[0], zs[0], grid, tol, False, src, 7.0)
+    ctx.close()
+
+
+def test_autotuned_context_keeps_the_window_path(fh, tmp_path):
+    ctx = fh.Context("fp64")
+    args = (24, 6.0, 12.0, 6.0, 6.0, 40, 12, 90, 40)
+    q = ctx.quad_starshade(*args)
+    grid = (200, 200, 0.024, 0.024)
+    path = str(tmp_path / "tune.jsonl")
+    best = ctx.autotune_grid(q, 5e-7, 3.7e7, *grid, cache_path=path)
+    assert best.spread_method in (1, 2, 3, 4, 5)
+    for c in (ctx, fh.Context("fp64")):
+        c.autotune_grid(q, 5e-7, 3.7e7, *grid, cache_path=path)
+        u = c.field_grid(q, 5e-7, 3.7e7, *grid)
+        check(u, oracle.quad_starshade(*args), 5e-7, 3.7e7, grid, 1e-9)
+    ctx.close()
