@@ -250,7 +250,7 @@ bool window_plan(fh_ctx* c, const T1Plan& pl, int B, const fh_quad* const* qs, s
     if (win_dft_lds(SX, (SY + 15) / 16, 16, sizeof(R)) > kLdsBudget) return false;
     // workgroups: as many as are resident at once, at least two batches of
     // 64 nodes per wavefront
-    const int64_t per_cu = std::min<int64_t>(3, kCuLds / (win_lds(SX, SY, pl.k.w, sizeof(R))));
+    const int64_t per_cu = std::min<int64_t>(4, kCuLds / (win_lds(SX, SY, pl.k.w, sizeof(R))));
     const int64_t resident = std::max<int64_t>(1, c->cu_count * per_cu / B);
     const int64_t enough = (Ntot / B + 128 * kWinWaves - 1) / (128 * kWinWaves);
     wg.nblk = (int)std::max<int64_t>(1, std::min(resident, enough));

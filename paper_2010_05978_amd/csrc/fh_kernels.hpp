@@ -1003,11 +1003,12 @@ __global__ void __launch_bounds__(256) k_spread_reg(const Sub* __restrict__ subs
 // updated four points at a time by v_mfma_{f64,f32}_16x16x4 (lane l supplies
 // A[row l % 16][point l / 16] and B[point l / 16][column l % 16]).
 //
-// The operands are read from zero-padded rows of kx and c ky (real and
-// imaginary) staged in LDS for MS points at a time, so that a lane reads its
-// value with no bounds test: each point's shifted row base is staged too.  The kernel values
-// are evaluated by lanes over the value index with the polynomial table (as
-// the wavefront spread does), the y values multiplied by the strength there.
+// The operands are read from zero-padded rows of kx and ky staged in LDS for
+// MS points at a time, so that a lane reads its value with no bounds test:
+// each point's shifted row bases are staged too, beside its strength, which a
+// lane multiplies into its x value on the way to the product.  The kernel
+// values are evaluated by lanes over the value index with the polynomial
+// table (as the wavefront spread does).
 // A point costs the same whatever its neighbours; the wavefront spread
 // instead merges runs of points that share a first cell, which wins where
 // points crowd.  Points are summed in their staged order, four at a time (the
@@ -1027,73 +1028,106 @@ template <> struct MfmaAcc<float> {
     __device__ static int row(int lane, int v) { return 4 * (lane >> 4) + v; }
 };
 
-constexpr int kMfmaWaves = 4;  // wavefronts (items) per block
 
-// Operand rows in LDS: the x values of the MS staged points lie in one array,
-// point q's W values at positions q P + T - 1 .. q P + T + W - 2 and zeros
-// elsewhere; the real and imaginary y rows (times the strength) follow in two
-// arrays of the same layout.  Lane i of the block b reads position
-// q P + T - 1 - cx + 16 b + i, which stays inside point q's window
-// [q P, q P + 16 NB + T - 2]: that window holds no other point's values when
-// the period P is at least 16 NB (and the tile side L <= 16 NB).  P is odd so
-// that consecutive points start in different LDS banks.
-__host__ __device__ inline int mfma_period(int NB) { return 16 * NB + 1; }
-__host__ __device__ inline int mfma_rows(int NB, int T, int MS) { return MS * mfma_period(NB) + T; }
 
-// LDS bytes of one wavefront's staging of MS points: three operand arrays,
-// the strengths and the polynomial arguments (2 reals each per point), and
-// two row offsets per point.
-__host__ __device__ inline size_t mfma_wave_lds(int NB, int T, int MS, size_t rsize)
+// Operand rows in LDS: argument a = 2 q (the x of staged point q) or 2 q + 1
+// (its y) has its W values at positions a P + T - 1 .. a P + T + W - 2 and
+// zeros elsewhere.  Lane i of the block b reads position
+// a P + T - 1 - c + 16 b + i, which stays inside the argument's window
+// [a P, a P + 16 NB + T - 2]: that window holds no other argument's values
+// when the period P is at least 16 NB (and the tile side L <= 16 NB).  Lanes
+// write a run of (W + 1)/2 values per argument, several arguments at a time,
+// and P exceeds 16 by as much, so that the runs of one write lie side by side
+// in the LDS banks.
+__host__ __device__ constexpr int mfma_period(int NB, int W) { return 16 * NB + poly_npair(W); }
+__host__ __device__ constexpr int mfma_rows(int NB, int T, int W, int MS)
 {
-    return (3 * (size_t)mfma_rows(NB, T, MS) + 4 * (size_t)MS) * rsize + 2 * (size_t)MS * sizeof(int);
+    return 2 * MS * mfma_period(NB, W) + 16 * NB + T;
 }
 
-// Kernel values of MS staged points by the mirrored pairs (lane (pg, pp) as in
-// k_spread_mfma): arguments 0..MS-1 are the points' x, whose values go to the
-// first operand array, the next MS their y, whose values times the strength
-// go to the second and third.
+// A staged point as the operand reads take it: its strength and the byte
+// offsets of its two rows' first operand (one 16-byte read in FP32, two in
+// FP64).
+template <class R> struct MfmaPoint;
+template <> struct MfmaPoint<double> {
+    double2 c;
+    int2 o;
+    static constexpr int words = 6;  // 4-byte words staged per point
+    __device__ static void put(unsigned char* base, int MS, int q, double2 c, int ox, int oy)
+    {
+        reinterpret_cast<double2*>(base)[q] = c;
+        reinterpret_cast<int2*>(base + 16 * MS)[q] = make_int2(ox, oy);
+    }
+    __device__ static MfmaPoint get(const unsigned char* base, int MS, int q)
+    {
+        return MfmaPoint{reinterpret_cast<const double2*>(base)[q],
+                         reinterpret_cast<const int2*>(base + 16 * MS)[q]};
+    }
+};
+template <> struct MfmaPoint<float> {
+    float2 c;
+    int2 o;
+    static constexpr int words = 4;
+    __device__ static void put(unsigned char* base, int, int q, float2 c, int ox, int oy)
+    {
+        reinterpret_cast<int4*>(base)[q] = make_int4(__float_as_int(c.x), __float_as_int(c.y), ox, oy);
+    }
+    __device__ static MfmaPoint get(const unsigned char* base, int, int q)
+    {
+        const int4 v = reinterpret_cast<const int4*>(base)[q];
+        return MfmaPoint{make_float2(__int_as_float(v.x), __int_as_float(v.y)), make_int2(v.z, v.w)};
+    }
+};
+
+// LDS bytes of one wavefront's staging of MS points: the points, their
+// polynomial arguments (2 reals each) and the operand rows.
+__host__ __device__ constexpr size_t mfma_wave_lds(int NB, int T, int W, int MS, size_t rsize)
+{
+    return ((rsize == 8 ? 24 : 16) * (size_t)MS + (2 * (size_t)MS + mfma_rows(NB, T, W, MS)) * rsize + 15) / 16 * 16;
+}
+
+// Kernel values of the MS staged points by the mirrored pairs (lane (pg, pp)
+// as in k_spread_mfma), into the operand rows.
 template <class R, int W, int MS>
-__device__ __forceinline__ void mfma_stage_values(R* rows, const R* ttab, const R* ctab, const R* ce, const R* co,
-                                                  int pg, int pp, int P, int T, int AL)
+__device__ __forceinline__ void mfma_stage_values(R* rows, const R* ttab, const R* ce, const R* co, int pg, int pp,
+                                                  int P, int T)
 {
     constexpr int NPAIR = poly_npair(W), NE = poly_ne(W), NO = poly_no(W);
     constexpr int KGP = 64 / NPAIR;
 #pragma unroll
     for (int r = 0; r < (2 * MS + KGP - 1) / KGP; ++r) {
-        const int qq = r * KGP + pg;
-        if (pg < KGP && qq < 2 * MS) {
-            const R t = ttab[qq], s2 = t * t;
+        const int a = r * KGP + pg;
+        if (pg < KGP && a < 2 * MS) {
+            const R t = ttab[a], s2 = t * t;
             R e = ce[0], o = co[0];
 #pragma unroll
             for (int j = 1; j < NE; ++j) e = e * s2 + ce[j];
 #pragma unroll
             for (int j = 1; j < NO; ++j) o = o * s2 + co[j];
-            const R lo = e + t * o, hi = e - t * o;  // cells pp and W - 1 - pp
-            const bool two = 2 * pp != W - 1;
-            const int q = qq < MS ? qq : qq - MS;
-            R* row = rows + q * P + T - 1;
-            if (qq < MS) {
-                row[pp] = lo;
-                if (two) row[W - 1 - pp] = hi;
-            } else {
-                const R cr = ctab[2 * q], ci = ctab[2 * q + 1];
-                row[AL + pp] = cr * lo;
-                row[2 * AL + pp] = ci * lo;
-                if (two) {
-                    row[AL + W - 1 - pp] = cr * hi;
-                    row[2 * AL + W - 1 - pp] = ci * hi;
-                }
-            }
+            R* row = rows + a * P + T - 1;
+            row[pp] = e + t * o;  // cells pp and W - 1 - pp
+            if (2 * pp != W - 1) row[W - 1 - pp] = e - t * o;
         }
     }
 }
 
-// The register allocator is asked for eight waves per SIMD in FP32 (61
-// registers; seven by default: batch spread 0.93 -> 0.88 ms) and four in
-// FP64, where the mirrored-pair evaluation would otherwise take 130
-// registers and three waves (2.40 -> 2.22 ms with four; five spill).
+// One wavefront per block: wavefronts share nothing, and alone each leaves
+// its place to the next as soon as its items are done (four to a block, 2.8
+// of the 4 places per SIMD were filled on average).  Matrix cores, VALU and
+// LDS are each busy for about a third of the time, so what counts is how many
+// wavefronts overlap: the register allocator is held to five per SIMD in FP64
+// (96 registers, eight spilled; six spill 22 and lose) and asked for eight in
+// FP32.  The 256-shape batch (51.7e6 nodes), spread alone: FP64 2.40 -> 2.13
+// ms with strengths multiplied into the x operand (a third operand array and
+// its writes gone, 31 LDS instructions per sixteen points instead of 52),
+// -> 1.76 ms with single wavefronts, two items each; FP32 0.93 -> 0.87 ->
+// 0.81 ms.  Loading the next stage's points early, across items, lost
+// (2.13 -> 2.29 ms: registers).
+// (2 x 2 blocks of accumulators take 64 registers more in FP64: two waves.)
+template <class R> constexpr int mfma_waves(int NB) { return NB == 1 ? (sizeof(R) == 4 ? 8 : 5) : (sizeof(R) == 4 ? 4 : 2); }
+
 template <class R, int W, int NB, int MS>
-__global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 8 : 4))) k_spread_mfma(const Sub* __restrict__ subs,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(mfma_waves<R>(NB)))) k_spread_mfma(const Sub* __restrict__ subs,
                                                                  const int* __restrict__ nsub_ptr,
                                                                  const uint32_t* __restrict__ cell,
                                                                  const typename V2<R>::T* __restrict__ dd,
@@ -1110,16 +1144,13 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
     static_assert(W <= 16 * NB, "the padded tile must fit the blocks");
     static_assert(MS % 16 == 0 && MS <= 64, "points are staged in sixteens, one per lane at most");
     extern __shared__ unsigned char smem_raw[];
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     const int T = gg.T, L = gg.L;
-    const int P = mfma_period(NB), AL = mfma_rows(NB, T, MS);
-    unsigned char* wbase = smem_raw + (size_t)wv * mfma_wave_lds(NB, T, MS, sizeof(R));
-    R* rows = reinterpret_cast<R*>(wbase);  // x values, y values (real), y values (imaginary)
-    R* ctab = rows + 3 * AL;                // strengths, 2 reals per point
-    R* ttab = ctab + 2 * MS;                // polynomial arguments: x of each point, then y
-    int* shx = reinterpret_cast<int*>(ttab + 2 * MS);  // byte offset of q P + T - 1 - cx
-    int* shy = shx + MS;                                // byte offset of q P + T - 1 - cy
+    constexpr int P = mfma_period(NB, W);
+    const int RL = mfma_rows(NB, T, W, MS);
+    unsigned char* pts = smem_raw;                                       // staged points
+    R* ttab = reinterpret_cast<R*>(pts + 4 * MfmaPoint<R>::words * MS);  // polynomial arguments, x and y of each
+    R* rows = ttab + 2 * MS;                                             // operand rows
     const int nsub = *nsub_ptr;
     const int k4 = lane >> 4, i16 = lane & 15;
     // With the table, lane (pg, pp), pp = lane % NPAIR, holds the even and
@@ -1137,9 +1168,9 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
 #pragma unroll
     for (int j = 0; j < NO; ++j) co[j] = has_poly ? poly[NP * W + (NE + j) * NPAIR + pp] : R(0);
     // rows start at zero; staging only ever writes their W middle positions
-    for (int e = lane; e < 3 * AL; e += 64) rows[e] = R(0);
+    for (int e = lane; e < RL; e += 64) rows[e] = R(0);
     const uint32_t lane_off = (uint32_t)(i16 * sizeof(R));
-    for (int s = blockIdx.x * kMfmaWaves + wv; s < nsub; s += gridDim.x * kMfmaWaves) {
+    for (int s = blockIdx.x; s < nsub; s += gridDim.x) {
         const Sub sb = subs[s];
         int ox, oy;
         tile_origin<R>(sb, gg, tpi, ox, oy);
@@ -1166,34 +1197,19 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
                     dv = dd[p];
                     cv = cc[p];
                 }
-                ctab[2 * lane] = cv.x;
-                ctab[2 * lane + 1] = cv.y;
-                ttab[lane] = R(2) * dv.x + R(W - 1);
-                ttab[MS + lane] = R(2) * dv.y + R(W - 1);
-                shx[lane] = (int)(sizeof(R) * (lane * P + T - 1 - cx));
-                shy[lane] = (int)(sizeof(R) * (AL + lane * P + T - 1 - cy));
+                MfmaPoint<R>::put(pts, MS, lane, cv, (int)(sizeof(R) * (2 * lane * P + T - 1 - cx)),
+                                  (int)(sizeof(R) * ((2 * lane + 1) * P + T - 1 - cy)));
+                reinterpret_cast<C*>(ttab)[lane] = C{R(2) * dv.x + R(W - 1), R(2) * dv.y + R(W - 1)};
             }
             wave_lds_order();
-            // the kernel values: arguments 0..MS-1 are the points' x, the
-            // next MS their y (times the strength)
             if (has_poly) {
-                mfma_stage_values<R, W, MS>(rows, ttab, ctab, ce, co, pg, pp, P, T, AL);
+                mfma_stage_values<R, W, MS>(rows, ttab, ce, co, pg, pp, P, T);
             } else {
 #pragma unroll
                 for (int r = 0; r < (2 * MS + KG - 1) / KG; ++r) {
-                    const int qq = r * KG + kg;
-                    if (kg < KG && qq < 2 * MS) {
-                        const R t = ttab[qq];
-                        const R k = es_one<R, W>((t - R(W - 1)) * R(0.5), ka, beta, nullptr);
-                        const int q = qq < MS ? qq : qq - MS;
-                        R* row = rows + q * P + T - 1 + ka;
-                        if (qq < MS) {
-                            row[0] = k;
-                        } else {
-                            row[AL] = ctab[2 * q] * k;
-                            row[2 * AL] = ctab[2 * q + 1] * k;
-                        }
-                    }
+                    const int a = r * KG + kg;
+                    if (kg < KG && a < 2 * MS)
+                        rows[a * P + T - 1 + ka] = es_one<R, W>((ttab[a] - R(W - 1)) * R(0.5), ka, beta, nullptr);
                 }
             }
             wave_lds_order();
@@ -1203,17 +1219,18 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
                 if (16 * h >= np) break;  // wavefront-uniform
                 // four points per product, the operands of all sixteen read
                 // first (points past np carry zero strength)
-                R bx[4][NB], ar[4][NB], ai[4][NB];
+                R ky[4][NB], kr[4][NB], ki[4][NB];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int q = 16 * h + 4 * g + k4;
-                    const unsigned char* px = reinterpret_cast<const unsigned char*>(rows) + shx[q] + lane_off;
-                    const unsigned char* py = reinterpret_cast<const unsigned char*>(rows) + shy[q] + lane_off;
+                    const MfmaPoint<R> pt = MfmaPoint<R>::get(pts, MS, 16 * h + 4 * g + k4);
+                    const unsigned char* px = reinterpret_cast<const unsigned char*>(rows) + pt.o.x + lane_off;
+                    const unsigned char* py = reinterpret_cast<const unsigned char*>(rows) + pt.o.y + lane_off;
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        bx[g][b] = reinterpret_cast<const R*>(px)[16 * b];
-                        ar[g][b] = reinterpret_cast<const R*>(py)[16 * b];
-                        ai[g][b] = reinterpret_cast<const R*>(py)[16 * b + AL];
+                        const R kx = reinterpret_cast<const R*>(px)[16 * b];
+                        kr[g][b] = pt.c.x * kx;
+                        ki[g][b] = pt.c.y * kx;
+                        ky[g][b] = reinterpret_cast<const R*>(py)[16 * b];
                     }
                 }
 #pragma unroll
@@ -1223,8 +1240,8 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
                     for (int br = 0; br < NB; ++br)
 #pragma unroll
                         for (int bc = 0; bc < NB; ++bc) {
-                            are[br][bc] = M::mma(ar[g][br], bx[g][bc], are[br][bc]);
-                            aim[br][bc] = M::mma(ai[g][br], bx[g][bc], aim[br][bc]);
+                            are[br][bc] = M::mma(ky[g][br], kr[g][bc], are[br][bc]);
+                            aim[br][bc] = M::mma(ky[g][br], ki[g][bc], aim[br][bc]);
                         }
                 }
             }
@@ -1247,10 +1264,10 @@ __global__ void __launch_bounds__(64 * kMfmaWaves) __attribute__((amdgpu_waves_p
 // Points staged per wavefront at a time.
 template <class R> constexpr int mfma_stage() { return 16; }
 
-// LDS bytes of one matrix-core spread block: the staging of each wavefront.
-inline size_t mfma_spread_lds(int NB, int T, size_t rsize)
+// LDS bytes of one matrix-core spread block.
+inline size_t mfma_spread_lds(int NB, int T, int W, size_t rsize)
 {
-    return (size_t)kMfmaWaves * mfma_wave_lds(NB, T, rsize == 8 ? mfma_stage<double>() : mfma_stage<float>(), rsize);
+    return mfma_wave_lds(NB, T, W, rsize == 8 ? mfma_stage<double>() : mfma_stage<float>(), rsize);
 }
 
 // ----------------------------------------------------------------- reduce
@@ -2406,7 +2423,7 @@ inline int spread_waves(const GridGeom& gg, size_t rsize)
 // LDS bytes of one spread block.
 inline size_t spread_lds(const GridGeom& gg, size_t rsize)
 {
-    if (gg.method == 5) return mfma_spread_lds(gg.L <= 16 ? 1 : 2, gg.T, rsize);
+    if (gg.method == 5) return mfma_spread_lds(gg.L <= 16 ? 1 : 2, gg.T, gg.W, rsize);
     if (gg.method == 4) {
         // staging of 32 points (W + KYP + 2 reals and 2 ints each) and the 4
         // wavefront tiles (see RegTile and reg_spread_lds)
@@ -2435,13 +2452,13 @@ void launch_spread_w(fh_ctx* c, unsigned grid, const Sub* subs, const int* nsub,
         // (T + W - 1) <= 32: two 16-cell blocks per dimension, else one
         if constexpr (W <= 16) {
             if (gg.L <= 16) {
-                hipLaunchKernelGGL((k_spread_mfma<R, W, 1, mfma_stage<R>()>), dim3(grid), dim3(64 * kMfmaWaves),
-                                   mfma_spread_lds(1, gg.T, sizeof(R)), c->stream, subs, nsub, cell, (const C2*)dd,
+                hipLaunchKernelGGL((k_spread_mfma<R, W, 1, mfma_stage<R>()>), dim3(grid), dim3(64),
+                                   mfma_spread_lds(1, gg.T, W, sizeof(R)), c->stream, subs, nsub, cell, (const C2*)dd,
                                    (const C2*)cc, slots, gg, tpi, (R)beta, (const R*)poly);
                 return;
             }
         }
-            hipLaunchKernelGGL((k_spread_mfma<R, W, 2, mfma_stage<R>()>), dim3(grid), dim3(64 * kMfmaWaves), mfma_spread_lds(2, gg.T, sizeof(R)),
+            hipLaunchKernelGGL((k_spread_mfma<R, W, 2, mfma_stage<R>()>), dim3(grid), dim3(64), mfma_spread_lds(2, gg.T, W, sizeof(R)),
                                c->stream, subs, nsub, cell, (const C2*)dd, (const C2*)cc, slots, gg, tpi, (R)beta,
                                (const R*)poly);
         return;
@@ -2666,11 +2683,11 @@ fh_status spread_items(fh_ctx* c, const InstParams& p0, const InstParams* table,
         // one block per work item up to a few waves of the whole chip
         // (wavefront blocks: as many as fit in LDS, at most 32 per CU)
         const int64_t per_cu = gg.method == 1 ? 8 : std::min<int64_t>(32, kCuLds / spread_lds(gg, sizeof(R)));
-        // (the matrix-core spread takes kMfmaWaves items per block)
-        const int64_t items_per_block = gg.method == 5 ? kMfmaWaves : 1;
-        const unsigned grid = (unsigned)std::max<int64_t>(
-            1, std::min<int64_t>((b.max_sub + items_per_block - 1) / items_per_block,
-                                 (int64_t)c->cu_count * std::max<int64_t>(1, per_cu) * 4));
+        // (single wavefronts of the matrix-core spread: as many more as take
+        // 512 nodes each, about two items of a batch)
+        int64_t most = (int64_t)c->cu_count * std::max<int64_t>(1, per_cu) * 4;
+        if (gg.method == 5) most = std::max(most, Ntot / 512);
+        const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(b.max_sub, most));
         FH_TRY(launch_spread<R>(c, grid, b.subs, b.nsub, b.cell, b.dd, b.cc, (typename V2<R>::T*)b.slots, gg, tpi,
                                 beta, poly));
     }
@@ -2800,7 +2817,7 @@ void spread_defaults(const fh_ctx* c, GridGeom& g, int auto_method = 2)
         g.method = 2;
     // the matrix-core spread holds at most 32 x 32 cells, and its staging
     // must fit the LDS budget
-    if (g.method == 5 && (g.L > 32 || mfma_spread_lds(g.L <= 16 ? 1 : 2, g.T, c->prec == FH_FP64 ? 8 : 4) > kLdsBudget))
+    if (g.method == 5 && (g.L > 32 || mfma_spread_lds(g.L <= 16 ? 1 : 2, g.T, g.W, c->prec == FH_FP64 ? 8 : 4) > kLdsBudget))
         g.method = 2;
     g.P = c->opt.max_subproblem > 0 ? c->opt.max_subproblem : 0;
 }

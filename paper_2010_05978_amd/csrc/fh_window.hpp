@@ -33,14 +33,14 @@ constexpr int kWinWaves = 4;  // wavefronts per workgroup
 // default), and one per wavefront in FP32, whose LDS atomics are slow.  Four
 // private FP64 windows of 27 x 27 cells leave LDS for two wavefronts per SIMD
 // only, and the staging's latency then shows: 998,400 nodes on 2048 x 2048
-// outputs 99.6 us, with the shared window 93.4 (three wavefronts per SIMD),
-// and 549 against 522 us for the gradient over three wavelengths.
+// outputs 99.6 us, with the shared window 93.4, and 549 against 522 us for
+// the gradient over three wavelengths.
 template <class R> constexpr int win_tiles() { return sizeof(R) == 8 ? 1 : kWinWaves; }
 
 __host__ __device__ inline size_t win_lds(int SX, int SY, int W, size_t rsize)
 {
     return (rsize == 8 ? 1 : kWinWaves) * ((size_t)SX * SY * 2 * rsize) +
-           kWinWaves * ((mfma_wave_lds(1, 17 - W, 16, rsize) + 15) / 16 * 16);
+           kWinWaves * mfma_wave_lds(1, 17 - W, W, 16, rsize);
 }
 
 // Minimum and maximum over each row of 16 lanes.
@@ -64,9 +64,10 @@ __device__ __forceinline__ int row_max16(int v) { return -row_min16(-v); }
 // zero.  Sixteen nodes that lie further apart are taken one by one, moving
 // as needed, so any order gives the same sums.
 // Bound by the operand staging (VALU and LDS), as k_spread_mfma; held to the
-// registers of three wavefronts per SIMD (held to four, 18 spill).
+// registers of four wavefronts per SIMD (14 spill in FP64; against three and
+// none, 86 and 88 us for 998,400 nodes on 2048 x 2048 outputs).
 template <class R, int W>
-__global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_per_eu(3))) k_win_spread(
+__global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_per_eu(4))) k_win_spread(
     InstParams p0, const InstParams* __restrict__ table, WinGeom wg, typename V2<R>::T* __restrict__ part,
     const R* __restrict__ poly)
 {
@@ -75,7 +76,7 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     using V = typename M::V;
     constexpr int MS = 16, T = 17 - W;
     constexpr int NP = poly_np(W), NPAIR = poly_npair(W), NE = poly_ne(W), NO = poly_no(W);
-    constexpr int P = 17, AL = MS * P + T;  // mfma_period(1), mfma_rows(1, T, MS)
+    constexpr int P = mfma_period(1, W), RL = mfma_rows(1, T, W, MS);
     static_assert(T >= 1, "the kernel must fit the matrix-core tile");
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -83,12 +84,9 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     const int SX = wg.SX, SY = wg.SY, cells = SX * SY;
     constexpr int NTILE = win_tiles<R>();
     C* tile = reinterpret_cast<C*>(smem_raw) + (NTILE > 1 ? wv : 0) * cells;
-    R* rows = reinterpret_cast<R*>(smem_raw + NTILE * cells * sizeof(C) +
-                                   wv * ((mfma_wave_lds(1, T, MS, sizeof(R)) + 15) / 16 * 16));
-    R* ctab = rows + 3 * AL;
-    R* ttab = ctab + 2 * MS;
-    int* shx = reinterpret_cast<int*>(ttab + 2 * MS);
-    int* shy = shx + MS;
+    unsigned char* pts = smem_raw + NTILE * cells * sizeof(C) + wv * mfma_wave_lds(1, T, W, MS, sizeof(R));
+    R* ttab = reinterpret_cast<R*>(pts + 4 * MfmaPoint<R>::words * MS);
+    R* rows = ttab + 2 * MS;
     const int pp = lane % NPAIR, pg = lane / NPAIR;
     R ce[NE], co[NO];
 #pragma unroll
@@ -97,7 +95,7 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     for (int j = 0; j < NO; ++j) co[j] = poly[NP * W + (NE + j) * NPAIR + pp];
     for (int e = threadIdx.x; e < NTILE * cells; e += 64 * kWinWaves)
         reinterpret_cast<C*>(smem_raw)[e] = C{R(0), R(0)};
-    for (int e = lane; e < 3 * AL; e += 64) rows[e] = R(0);
+    for (int e = lane; e < RL; e += 64) rows[e] = R(0);
     __syncthreads();
     const int b = blockIdx.y;
     const InstParams ip = table ? table[b] : p0;
@@ -176,51 +174,48 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
             const int np = min(MS, np64 - MS * s);
             if (np <= 0) break;  // wavefront-uniform
             const bool mine = k4 == s;
-            if (mine) {
-                ctab[2 * i16] = (R)cr;
-                ctab[2 * i16 + 1] = (R)ci;
-                ttab[i16] = R(2) * (R)d1 + R(W - 1);
-                ttab[MS + i16] = R(2) * (R)d2 + R(W - 1);
-            }
-            wave_lds_order();
-            mfma_stage_values<R, W, MS>(rows, ttab, ctab, ce, co, pg, pp, P, T, AL);
             const int mnx = lane_val(rnx, MS * s), mxx = lane_val(rxx, MS * s);
             const int mny = lane_val(rny, MS * s), mxy = lane_val(rxy, MS * s);
-            if (mxx - mnx < T && mxy - mny < T) {
-                if (mnx < ox || mxx >= ox + T || mny < oy || mxy >= oy + T)
-                    move_to(place(mnx, mxx, SX), place(mny, mxy, SY));
-                if (mine) {
-                    // nodes past the run's end carry zero strength anywhere
-                    shx[i16] = (int)(sizeof(R) * (i16 * P + T - 1 - (live ? l1 - ox : 0)));
-                    shy[i16] = (int)(sizeof(R) * (AL + i16 * P + T - 1 - (live ? l2 - oy : 0)));
-                }
-                wave_lds_order();
-                R bx[4], ar[4], ai[4];
+            const bool together = mxx - mnx < T && mxy - mny < T;
+            if (together && (mnx < ox || mxx >= ox + T || mny < oy || mxy >= oy + T))
+                move_to(place(mnx, mxx, SX), place(mny, mxy, SY));
+            if (mine) {
+                // nodes past the run's end carry zero strength anywhere; nodes
+                // taken one by one find their rows' first value here
+                const int rx = live && together ? l1 - ox : 0, ry = live && together ? l2 - oy : 0;
+                MfmaPoint<R>::put(pts, MS, i16, C{(R)cr, (R)ci}, (int)(sizeof(R) * (2 * i16 * P + T - 1 - rx)),
+                                  (int)(sizeof(R) * ((2 * i16 + 1) * P + T - 1 - ry)));
+                reinterpret_cast<C*>(ttab)[i16] = C{R(2) * (R)d1 + R(W - 1), R(2) * (R)d2 + R(W - 1)};
+            }
+            wave_lds_order();
+            mfma_stage_values<R, W, MS>(rows, ttab, ce, co, pg, pp, P, T);
+            wave_lds_order();
+            if (together) {
+                R ky[4], kr[4], ki[4];
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int q = 4 * g + k4;
-                    const unsigned char* px = reinterpret_cast<const unsigned char*>(rows) + shx[q] + lane_off;
-                    const unsigned char* py = reinterpret_cast<const unsigned char*>(rows) + shy[q] + lane_off;
-                    bx[g] = reinterpret_cast<const R*>(px)[0];
-                    ar[g] = reinterpret_cast<const R*>(py)[0];
-                    ai[g] = reinterpret_cast<const R*>(py)[AL];
+                    const MfmaPoint<R> pt = MfmaPoint<R>::get(pts, MS, 4 * g + k4);
+                    const R kx = *reinterpret_cast<const R*>(reinterpret_cast<const unsigned char*>(rows) + pt.o.x + lane_off);
+                    ky[g] = *reinterpret_cast<const R*>(reinterpret_cast<const unsigned char*>(rows) + pt.o.y + lane_off);
+                    kr[g] = pt.c.x * kx;
+                    ki[g] = pt.c.y * kx;
                 }
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    are = M::mma(ar[g], bx[g], are);
-                    aim = M::mma(ai[g], bx[g], aim);
+                    are = M::mma(ky[g], kr[g], are);
+                    aim = M::mma(ky[g], ki[g], aim);
                 }
             } else {
-                wave_lds_order();
                 for (int q = 0; q < np; ++q) {
                     const int cx = lane_val(l1, MS * s + q), cy = lane_val(l2, MS * s + q);
                     if (cx < ox || cx >= ox + T || cy < oy || cy >= oy + T)
                         move_to(place(cx, cx, SX), place(cy, cy, SY));
                     // the node alone: the other three of the product are zero
-                    const R bx = rows[q * P + T - 1 - (cx - ox) + i16];
-                    const R* py = rows + AL + q * P + T - 1 - (cy - oy) + i16;
-                    are = M::mma(k4 == 0 ? py[0] : R(0), bx, are);
-                    aim = M::mma(k4 == 0 ? py[AL] : R(0), bx, aim);
+                    const MfmaPoint<R> pt = MfmaPoint<R>::get(pts, MS, q);
+                    const R kx = rows[2 * q * P + T - 1 - (cx - ox) + i16];
+                    const R ky = k4 == 0 ? rows[(2 * q + 1) * P + T - 1 - (cy - oy) + i16] : R(0);
+                    are = M::mma(ky, pt.c.x * kx, are);
+                    aim = M::mma(ky, pt.c.y * kx, aim);
                 }
             }
             // the next sixteen rewrite the staging
