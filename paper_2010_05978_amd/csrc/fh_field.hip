@@ -478,19 +478,19 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     auto run = [&]() -> fh_status {
         timing_mark(c, 0);
         if (rebuild) FH_TRY(rules_launch(c, drules, rules_coef, nrules, rule_blocks));
+        const EpiParams ep{n1, n2, gg.nf1, gg.nf2, h1, h2, xc, yc, ip1, ip2};
+        RowFactors rf;
+        if (lc.C > 0) rf = RowFactors{ep, epi[0], batched ? (const EpiInst*)depi : nullptr, E2, (int64_t)B * n2};
         if (fused) {
-            FH_TRY(spread_items<R>(c, inst[0], batched ? dinst : nullptr, B, Ntot, gg, sb, pl.k.beta, pl.k.poly));
+            FH_TRY(spread_items<R>(c, inst[0], batched ? dinst : nullptr, B, Ntot, gg, sb, pl.k.beta, pl.k.poly, rf));
             FH_TRY(launch_t1_rows<R>(c, lr, reach, B, (gg.rows + lr.C - 1) / lr.C, gg, sb, n1, F));
             c->tile_cnt_dirty = false;
         } else {
             FH_TRY(run_spread<R>(c, inst[0], batched ? dinst : nullptr, B, Ntot, gg, sb, F, pl.k.beta, pl.k.poly,
-                                 ragged ? (const int2*)drwin : nullptr, total_rows));
+                                 ragged ? (const int2*)drwin : nullptr, total_rows, rf));
             if (total_rows > 0) FH_TRY(fft_exec(c, fa, F));
         }
-        EpiParams ep{n1, n2, gg.nf1, gg.nf2, h1, h2, xc, yc, ip1, ip2};
         if (lc.C > 0) {
-            hipLaunchKernelGGL(k_t1_rowfactors, dim3(nblocks(n2, 256), B), dim3(256), 0, c->stream, ep, epi[0],
-                               batched ? (const EpiInst*)depi : nullptr, E2);
             timing_mark(c, 3);
             const int groups = (n1 + lc.C - 1) / lc.C;
             FH_LDS_LAUNCH(k_t1_cols, R, lc, dim3(xcd_blocks(groups), B), c->stream, F, u, gg.rows,

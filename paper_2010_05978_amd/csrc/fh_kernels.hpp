@@ -24,8 +24,7 @@ template <> struct V2<float> { using T = float2; };
 template <> struct V2<double> { using T = double2; };
 
 constexpr int kMaxSubPerTile = 2048;  // work items per tile before items grow
-constexpr int kMergeG = 16;           // slots summed per merge group
-constexpr int kMergeLevels = 2;       // 16 * 16 * 16 >= kMaxSubPerTile
+constexpr int kMergeG = 16;           // slots of a tile that its reduce still sums itself
 constexpr size_t kLdsBudget = 64 * 1024;
 constexpr size_t kCuLds = 160 * 1024;  // LDS per CU
 
@@ -396,11 +395,67 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_sums(const int* __restric
     }
 }
 
+// ------------------------------------------------- type-1 epilogue inputs
+struct EpiInst {
+    double inv2lz;  // 1/(2 lambda z): target chirp in turns
+    double invlz;   // 1/(lambda z)
+    int occ;
+    int sh2;        // row shift of the instance's window
+    int rows;       // rows held for the instance (its window)
+    int roff;       // its first row in the band array
+    int sh1;        // column shift (k_win_dft)
+};
+
+struct EpiParams {
+    int n1, n2, nf1, nf2;
+    double h1, h2, xc, yc;
+    const double* iphi1;
+    const double* iphi2;
+};
+
+// Row factors of the type-1 epilogue, once per call: for instance b and
+// output row k2, E2 = exp(i pi eta^2/(lambda z) - 2 pi i k2 sh2/nf2)/Phi2(k2)
+// with each phase reduced in turns before sincospi.  They depend on the
+// call's parameters alone and are computed by blocks of the tile scan's
+// launch (count: B n2 of them, 0: none), which leaves most of the chip idle.
+struct RowFactors {
+    EpiParams ep{};
+    EpiInst e0{};
+    const EpiInst* table = nullptr;
+    double2* E2 = nullptr;
+    int64_t count = 0;
+};
+
+__device__ __forceinline__ void row_factor(const RowFactors& rf, int64_t i)
+{
+    if (i >= rf.count) return;
+    const int n2 = rf.ep.n2, nf2 = rf.ep.nf2;
+    const int b = (int)(i / n2), k2i = (int)(i - (int64_t)b * n2);
+    const EpiInst ei = rf.table ? rf.table[b] : rf.e0;
+    const int sm = (int)(((long long)ei.sh2 % nf2 + nf2) % nf2);
+    const int k2 = k2i - n2 / 2;
+    const double y = rf.ep.yc + rf.ep.h2 * k2;
+    double tt = y * y * ei.inv2lz;
+    const unsigned km = (unsigned)(k2 < 0 ? k2 + nf2 : k2);
+    const unsigned ph = (km * (unsigned)sm) % (unsigned)nf2;
+    tt = (tt - rint(tt)) - (double)ph / (double)nf2;
+    tt -= rint(tt);
+    double sn, cs;
+    sincospi(2.0 * tt, &sn, &cs);
+    const double sc = rf.ep.iphi2[k2i];
+    rf.E2[i] = make_double2(cs * sc, sn * sc);
+}
+
 __global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const int* __restrict__ cnt, int ntiles, int P,
                                                              const int* __restrict__ bsum,
                                                              int* __restrict__ off, int* __restrict__ tsub,
-                                                             int* __restrict__ nsub_out, int* __restrict__ zero_out)
+                                                             int* __restrict__ nsub_out, int* __restrict__ zero_out,
+                                                             int nscan, RowFactors rf)
 {
+    if ((int)blockIdx.x >= nscan) {
+        row_factor(rf, (int64_t)((int)blockIdx.x - nscan) * kScanThreads + threadIdx.x);
+        return;
+    }
     // the counter of the tile reduce's list starts at zero
     if (zero_out && blockIdx.x == 0 && threadIdx.x == 0) *zero_out = 0;
     __shared__ int wa[16], wb[16];
@@ -437,7 +492,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_tiles(const int* __restri
         ea += c[k];
         eb += ns;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *nsub_out = base_b + tb;
+    if ((int)blockIdx.x == nscan - 1 && threadIdx.x == 0) *nsub_out = base_b + tb;
 }
 
 // Stable binning: after the sort by tile (ties in node order), the node at
@@ -1271,72 +1326,87 @@ inline size_t mfma_spread_lds(int NB, int T, int W, size_t rsize)
 }
 
 // ----------------------------------------------------------------- reduce
-// A tile with cnt work items is merged in levels: level l sums, for every
-// item r (its index within the tile) divisible by G^l, the slots r + k G^(l-1)
-// (k < G, inside the tile) into slot r.  A tile takes merge_levels(cnt)
-// levels, which leaves at most G heads, at stride G^levels, for the reduce.
-// Groups are disjoint within a level and the order of every sum is fixed.
-__host__ __device__ __forceinline__ int merge_levels(int cnt)
-{
-    int l = 0;
-    for (int span = kMergeG; cnt > span && l < kMergeLevels; span *= kMergeG) ++l;
-    return l;
-}
-
-// A block takes kMergeChunk consecutive work items at a time: a thread per
-// item checks whether the item heads a group at this level (most items do
-// not: only crowded tiles merge) and the block lists those in LDS; then its
-// threads sum the listed groups, a thread per (group, slot element).  The
-// chunk is small so that the consecutive heads of one crowded tile spread
-// over many blocks.
-constexpr int kMergeChunk = 32;
+// The slots of a tile with more than kMergeG work items are summed into its
+// first before the reduce.  A block takes kMergeChunk consecutive work items
+// at a time; where a crowded tile has items ra .. rb - 1 of its n among them,
+// the block sums all n slots over the share [LL ra/n, LL rb/n) of their
+// elements, so that a tile gets blocks in proportion to its slots and one
+// launch does what levels of groups would need two for.  A thread per
+// (lane of items, element): the lanes take every IL-th slot, sixteen loads in
+// flight, and are added in lane order.  Shares are disjoint, and the order of
+// every sum is fixed.
+// Chunks of 32 items with 256 threads, which leave a share of hundreds of
+// elements to lanes that walk a hundred slots each, were slower than two
+// launches of levels (the sweep of 50 x 60,000 targets 3.61 -> 3.72 ms);
+// chunks of 8 with 512 threads sum a crowded tile in a round or two of loads:
+// 3.56 -> 3.30 ms, one launch fewer, and the starfish on 1000 x 1000 88.9 ->
+// 82.1 us together with the row factors that moved into the scan's launch.
+constexpr int kMergeChunk = 8;
+constexpr int kMergeThreads = 512;
+constexpr int kMergeLoads = 16;  // loads in flight per thread
 
 template <class R>
-__global__ void __launch_bounds__(256) k_merge_slots(typename V2<R>::T* __restrict__ slots,
+__global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T* __restrict__ slots,
                                                      const Sub* __restrict__ subs, const int* __restrict__ nsub_ptr,
-                                                     const int* __restrict__ tsub, int LL, int level)
+                                                     const int* __restrict__ tsub, int LL)
 {
     using C = typename V2<R>::T;
-    __shared__ int s_item[kMergeChunk];
-    __shared__ int s_nk[kMergeChunk];
+    __shared__ int4 s_job[kMergeChunk];  // first slot, slots, first element, past the last
     __shared__ int s_n;
+    __shared__ C s_acc[kMergeThreads];
     const int nsub = *nsub_ptr;
-    int stride = 1;
-    for (int l = 1; l < level; ++l) stride *= kMergeG;
-    const int span = stride * kMergeG;
-    const size_t st = (size_t)stride * LL;
-    const FastDiv dLL = fast_div((unsigned)LL);
     for (int i0 = blockIdx.x * kMergeChunk; i0 < nsub; i0 += gridDim.x * kMergeChunk) {
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
         const int i = i0 + (int)threadIdx.x;
         if (threadIdx.x < kMergeChunk && i < nsub) {
             const int t = subs[i].tile;
-            const int first = tsub[2 * t], cnt = tsub[2 * t + 1];
-            const int r = i - first;
-            if (merge_levels(cnt) >= level && r % span == 0) {
+            const int first = tsub[2 * t], n = tsub[2 * t + 1];
+            const int ra = i - first;
+            if (n > kMergeG && (ra == 0 || threadIdx.x == 0)) {
+                const int rb = min(n, ra + kMergeChunk - (int)threadIdx.x);
                 const int m = atomicAdd(&s_n, 1);
-                s_item[m] = i;
-                s_nk[m] = min(kMergeG, (cnt - r + stride - 1) / stride);
+                s_job[m] = make_int4(first, n, (int)((int64_t)LL * ra / n), (int)((int64_t)LL * rb / n));
             }
         }
         __syncthreads();
-        const int n = s_n;
-        for (int w = threadIdx.x; w < n * LL; w += blockDim.x) {
-            const int m = (int)fdiv((unsigned)w, dLL), e = w - m * LL;
-            const int nk = s_nk[m];
-            C* sp = slots + (size_t)s_item[m] * LL + e;
-            // all loads of the group in flight at once, then summed in order
-            C v[kMergeG];
+        const int nj = s_n;
+        for (int j = 0; j < nj; ++j) {
+            const int4 job = s_job[j];
+            const int n = job.y, ne = job.w - job.z;
+            if (ne <= 0) continue;  // block-uniform
+            const int IL = max(1, min(64, kMergeThreads / ne));
+            for (int eb = 0; eb < ne; eb += kMergeThreads) {
+                const int w = min(ne - eb, kMergeThreads);  // elements of this pass (all of them when IL > 1)
+                const int il = (int)threadIdx.x / w, e = job.z + eb + (int)threadIdx.x - il * w;
+                C a{R(0), R(0)};
+                if (il < IL) {
+                    const C* sp = slots + (size_t)job.x * LL + e;
+                    for (int k = il; k < n; k += kMergeLoads * IL) {
+                        C v[kMergeLoads];
 #pragma unroll
-            for (int k = 0; k < kMergeG; ++k) v[k] = k < nk ? sp[k * st] : C{R(0), R(0)};
-            C acc = v[0];
+                        for (int u = 0; u < kMergeLoads; ++u)
+                            v[u] = k + u * IL < n ? sp[(size_t)(k + u * IL) * LL] : C{R(0), R(0)};
 #pragma unroll
-            for (int k = 1; k < kMergeG; ++k) {
-                acc.x += v[k].x;
-                acc.y += v[k].y;
+                        for (int u = 0; u < kMergeLoads; ++u) {
+                            a.x += v[u].x;
+                            a.y += v[u].y;
+                        }
+                    }
+                }
+                if (IL > 1) {
+                    s_acc[threadIdx.x] = a;
+                    __syncthreads();
+                    if (il == 0)
+                        for (int k = 1; k < IL; ++k) {
+                            const C v = s_acc[k * w + threadIdx.x];
+                            a.x += v.x;
+                            a.y += v.y;
+                        }
+                }
+                if (il == 0) slots[(size_t)job.x * LL + e] = a;
+                __syncthreads();
             }
-            sp[0] = acc;
         }
         __syncthreads();
     }
@@ -1394,10 +1464,9 @@ __global__ void __launch_bounds__(256) k_reduce_tiles(const typename V2<R>::T* _
         const int2 rw = inst_rows(rwin, gg, b);
         const int wx = min(T, gg.nf1 - tx * T), wy = min(T, rw.x - ty * T);
         if (wy <= 0) continue;
-        // covering tile i = (dy, dx): its first merged slot, slot stride
-        // and number of merged slots (0 where no tile reaches), and the
+        // covering tile i = (dy, dx): its first slot and number of merged slots (0 where no tile reaches), and the
         // shift of its padded cells when it wraps around the period
-        int first[NC], stride[NC], heads[NC], sx[NC], sy[NC];
+        int first[NC], heads[NC], sx[NC], sy[NC];
         bool any = false;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
@@ -1411,10 +1480,7 @@ __global__ void __launch_bounds__(256) k_reduce_tiles(const typename V2<R>::T* _
             const int t = b * tpi + sty * gg.ntx + stx;
             const int n = ok ? tsub[2 * t + 1] : 0;
             first[i] = ok ? tsub[2 * t] : 0;
-            int st = 1;
-            for (int l = merge_levels(n); l > 0; --l) st *= kMergeG;
-            stride[i] = st;
-            heads[i] = (n + st - 1) / st;
+            heads[i] = n > kMergeG ? 1 : n;  // a crowded tile's slots are merged into its first
             any = any || n > 0;
         }
         C* out = Fv + ((size_t)rw.y + (size_t)ty * T) * gg.nf1 + (size_t)tx * T;
@@ -1435,7 +1501,7 @@ __global__ void __launch_bounds__(256) k_reduce_tiles(const typename V2<R>::T* _
                 const C* sp = slots + (size_t)first[i] * LL + (in ? ly * L + lx : 0);
 #pragma unroll
                 for (int u = 0; u < kRedU; ++u)
-                    r[q][i][u] = in && u < heads[i] ? sp[(size_t)u * stride[i] * LL] : C{R(0), R(0)};
+                    r[q][i][u] = in && u < heads[i] ? sp[(size_t)u * LL] : C{R(0), R(0)};
             }
 #pragma unroll
         for (int q = 0; q < KC; ++q) {
@@ -1452,12 +1518,11 @@ __global__ void __launch_bounds__(256) k_reduce_tiles(const typename V2<R>::T* _
                     const int dy = i / (REACH + 1), dx = i % (REACH + 1);
                     const int lx = ci[q] + dx * T - sx[i], ly = cj[q] + dy * T - sy[i];
                     const bool in = cv[q] && lx < L && ly < L;
-                    const size_t st = (size_t)stride[i] * LL;
                     const C* sp = slots + (size_t)first[i] * LL + (in ? ly * L + lx : 0);
                     for (int k = kRedU; k < heads[i]; k += 4) {
                         C v[4];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) v[u] = in && k + u < heads[i] ? sp[(k + u) * st] : C{R(0), R(0)};
+                        for (int u = 0; u < 4; ++u) v[u] = in && k + u < heads[i] ? sp[(size_t)(k + u) * LL] : C{R(0), R(0)};
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
                             ar += v[u].x;
@@ -1515,14 +1580,8 @@ __global__ void __launch_bounds__(256) k_tile_active(const int* __restrict__ tsu
     if (any) list[base + __popcll(m & ((1ull << lane) - 1ull))] = tile;
 }
 
-// Merged slots of a tile with n work items: (first item, number of merged
-// slots, item stride between them).
-__device__ __forceinline__ int4 tile_heads(int first, int n)
-{
-    int st = 1;
-    for (int l = merge_levels(n); l > 0; --l) st *= kMergeG;
-    return make_int4(first, (n + st - 1) / st, st, 0);
-}
+// Merged slots of a tile with n work items: (first item, number of them).
+__device__ __forceinline__ int4 tile_heads(int first, int n) { return make_int4(first, n > kMergeG ? 1 : n, 0, 0); }
 
 // Sum at cell (ci, cj) of tile (tx, ty) of one instance: the merged slots of
 // the tiles whose padded tiles cover it, covering tiles in (dy, dx) order,
@@ -1537,7 +1596,7 @@ __device__ __forceinline__ typename V2<R>::T reduce_cell(const typename V2<R>::T
     using C = typename V2<R>::T;
     constexpr int NC = (REACH + 1) * (REACH + 1);
     const int T = gg.T, L = gg.L, LL = L * L;
-    int first[NC], stride[NC], heads[NC], off[NC];
+    int first[NC], heads[NC], off[NC];
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
         const int dy = i / (REACH + 1), dx = i % (REACH + 1);
@@ -1552,10 +1611,9 @@ __device__ __forceinline__ typename V2<R>::T reduce_cell(const typename V2<R>::T
         }
         const int lx = ci + dx * T - sx, ly = cj + dy * T - sy;
         const bool in = okr && lx < L && ly < L;
-        const int4 h = in ? head(sty, stx) : make_int4(0, 0, 1, 0);
+        const int4 h = in ? head(sty, stx) : make_int4(0, 0, 0, 0);
         first[i] = h.x;
         heads[i] = h.y;
-        stride[i] = h.z;
         off[i] = in ? ly * L + lx : 0;
     }
     C r[NC][U];
@@ -1563,7 +1621,7 @@ __device__ __forceinline__ typename V2<R>::T reduce_cell(const typename V2<R>::T
     for (int i = 0; i < NC; ++i)
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            r[i][u] = u < heads[i] ? slots[((size_t)first[i] + (size_t)u * stride[i]) * LL + off[i]] : C{R(0), R(0)};
+            r[i][u] = u < heads[i] ? slots[((size_t)first[i] + u) * LL + off[i]] : C{R(0), R(0)};
     R ar = R(0), ai = R(0);
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -1573,7 +1631,7 @@ __device__ __forceinline__ typename V2<R>::T reduce_cell(const typename V2<R>::T
             ai += r[i][u].y;
         }
         for (int q = U; q < heads[i]; ++q) {
-            const C v = slots[((size_t)first[i] + (size_t)q * stride[i]) * LL + off[i]];
+            const C v = slots[((size_t)first[i] + q) * LL + off[i]];
             ar += v.x;
             ai += v.y;
         }
@@ -1639,7 +1697,7 @@ __global__ void __launch_bounds__(256) k_reduce_list(const typename V2<R>::T* __
             const int b = tile / tpi, tl = tile - b * tpi;
             const int ty = tl / gg.ntx, tx = tl - ty * gg.ntx;
             int sty = ty - dy;
-            int4 hv = make_int4(0, 0, 1, 0);
+            int4 hv = make_int4(0, 0, 0, 0);
             if (sty >= 0 || gg.wrap_y) {
                 if (sty < 0) sty = ((sty % gg.nty) + gg.nty) % gg.nty;
                 const int stx = (((tx - dx) % gg.ntx) + gg.ntx) % gg.ntx;
@@ -1717,7 +1775,7 @@ __global__ void __launch_bounds__(256) k_reduce_strips(const typename V2<R>::T* 
     for (int e = threadIdx.x; e < (REACH + 1) * ntx; e += blockDim.x) {
         const int k = e / ntx, tx = e - k * ntx;
         int sty = ty_lo + k;
-        int4 h = make_int4(0, 0, 1, 0);
+        int4 h = make_int4(0, 0, 0, 0);
         if (sty >= 0 || gg.wrap_y) {
             if (sty < 0) sty = ((sty % gg.nty) + gg.nty) % gg.nty;
             const int t = b * tpi + sty * ntx + tx;
@@ -1794,7 +1852,7 @@ __global__ void __launch_bounds__(NT) k_t1_rows(const typename V2<R>::T* __restr
     for (int e = threadIdx.x; e < nt * gg.ntx; e += NT) {
         const int k = e / gg.ntx, tx = e - k * gg.ntx;
         int sty = ty_lo + k;
-        int4 h = make_int4(0, 0, 1, 0);
+        int4 h = make_int4(0, 0, 0, 0);
         if (sty < gg.nty && (sty >= 0 || gg.wrap_y)) {
             if (sty < 0) sty = ((sty % gg.nty) + gg.nty) % gg.nty;
             const int t = b * tpi + sty * gg.ntx + tx;
@@ -1829,23 +1887,6 @@ __global__ void __launch_bounds__(NT) k_t1_rows(const typename V2<R>::T* __restr
 }
 
 // --------------------------------------------------------- type-1 finish
-struct EpiInst {
-    double inv2lz;  // 1/(2 lambda z): target chirp in turns
-    double invlz;   // 1/(lambda z)
-    int occ;
-    int sh2;        // row shift of the instance's window
-    int rows;       // rows held for the instance (its window)
-    int roff;       // its first row in the band array
-    int sh1;        // column shift (k_win_dft)
-};
-
-struct EpiParams {
-    int n1, n2, nf1, nf2;
-    double h1, h2, xc, yc;
-    const double* iphi1;
-    const double* iphi2;
-};
-
 // Z[b][c][r] = F[b][r][k1 mod nf1] with k1 = c - n1/2 for r < rows, 0 beyond:
 // the n1 needed columns after the first FFT pass, transposed and padded to
 // the full period for the second pass.
@@ -1951,30 +1992,6 @@ __global__ void __launch_bounds__(256) k_epilogue_t1(const R* __restrict__ Z, R*
     }
 }
 
-// Row factors of the type-1 epilogue, once per call: for instance b and
-// output row k2, E2 = exp(i pi eta^2/(lambda z) - 2 pi i k2 sh2/nf2)/Phi2(k2)
-// with each phase reduced in turns before sincospi.
-__global__ void __launch_bounds__(256) k_t1_rowfactors(EpiParams ep, EpiInst e0, const EpiInst* __restrict__ table,
-                                                       double2* __restrict__ E2)
-{
-    const int k2i = blockIdx.x * blockDim.x + threadIdx.x, b = blockIdx.y;
-    if (k2i >= ep.n2) return;
-    const EpiInst ei = table ? table[b] : e0;
-    const int nf2 = ep.nf2;
-    const int sm = (int)(((long long)ei.sh2 % nf2 + nf2) % nf2);
-    const int k2 = k2i - ep.n2 / 2;
-    const double y = ep.yc + ep.h2 * k2;
-    double tt = y * y * ei.inv2lz;
-    const unsigned km = (unsigned)(k2 < 0 ? k2 + nf2 : k2);
-    const unsigned ph = (km * (unsigned)sm) % (unsigned)nf2;
-    tt = (tt - rint(tt)) - (double)ph / (double)nf2;
-    tt -= rint(tt);
-    double sn, cs;
-    sincospi(2.0 * tt, &sn, &cs);
-    const double sc = ep.iphi2[k2i];
-    E2[(size_t)b * ep.n2 + k2i] = make_double2(cs * sc, sn * sc);
-}
-
 // Type-1 second pass and epilogue in one kernel.  Workgroup (group g,
 // instance b) takes the C output columns k1 + n1/2 in [g C, g C + C): it
 // loads their band of `rows` values from F (after the first pass over the
@@ -1983,7 +2000,7 @@ __global__ void __launch_bounds__(256) k_t1_rowfactors(EpiParams ep, EpiInst e0,
 // zero-pads each to nf2 in LDS, transforms, and writes
 // u[b][k2][k1] = epilogue(column value at k2 mod nf2) for every k2, with the
 // factors of k_epilogue_t1: its column factors here, its row factors from
-// k_t1_rowfactors.
+// row_factor.
 template <class R, int MAXE, int NT, bool R7>
 __global__ void __launch_bounds__(NT) k_t1_cols(const R* __restrict__ F, R* __restrict__ u, int rows, int ldf,
                                                             int compact, int C, int groups, LdsFftPlan plan, EpiParams ep,
@@ -2050,7 +2067,7 @@ __global__ void __launch_bounds__(NT) k_t1_cols(const R* __restrict__ F, R* __re
     __syncthreads();
     lds_fft<MAXE, NT, R7>(buf, plan, C, buf + lds_span(plan.n, C));
     // epilogue: C lanes write C consecutive outputs of a row, with the row
-    // factors of k_t1_rowfactors and the column factors above
+    // factors of row_factor and the column factors above
     const double2* E2 = E2all + (size_t)b * ep.n2;
     C2* uv = reinterpret_cast<C2*>(u) + (size_t)b * ep.n2 * ep.n1;
     for (int e = threadIdx.x; e < ep.n2 * C; e += NT) {
@@ -2638,7 +2655,8 @@ inline int tile_reach(const GridGeom& gg)
 // (the reduce follows: reduce_grid, or the type-1 row pass that fuses it).
 template <class R>
 fh_status spread_items(fh_ctx* c, const InstParams& p0, const InstParams* table, int ninst, int64_t Ntot,
-                       const GridGeom& gg, const SpreadBufs& b, double beta, const void* poly)
+                       const GridGeom& gg, const SpreadBufs& b, double beta, const void* poly,
+                       const RowFactors& rf = RowFactors{})
 {
     const int tpi = gg.ntx * gg.nty;
     const int ntiles_total = tpi * ninst;
@@ -2667,8 +2685,9 @@ fh_status spread_items(fh_ctx* c, const InstParams& p0, const InstParams* table,
     if (nscan > 1)
         hipLaunchKernelGGL(k_scan_sums, dim3(nscan), dim3(kScanThreads), 0, c->stream, b.cnt, ntiles_total, gg.P,
                            b.bsum);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(nscan), dim3(kScanThreads), 0, c->stream, b.cnt, ntiles_total, gg.P,
-                       b.bsum, b.off, b.tsub, b.nsub, b.nlist);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(nscan + (rf.count > 0 ? nblocks(rf.count, kScanThreads) : 0)),
+                       dim3(kScanThreads), 0, c->stream, b.cnt, ntiles_total, gg.P, b.bsum, b.off, b.tsub, b.nsub,
+                       b.nlist, nscan, rf);
     if (Ntot > 0 && b.key)
         hipLaunchKernelGGL(k_rank_sorted, dim3(nblocks(Ntot, 256)), dim3(256), 0, c->stream, b.key_sorted,
                            b.vals_sorted, Ntot, b.off, b.rank);
@@ -2697,9 +2716,8 @@ fh_status spread_items(fh_ctx* c, const InstParams& p0, const InstParams* table,
         const unsigned mgrid =
             (unsigned)std::max<int64_t>(1, std::min<int64_t>((b.max_sub + kMergeChunk - 1) / kMergeChunk,
                                                             (int64_t)c->cu_count * 16));
-        for (int level = 1; level <= kMergeLevels; ++level)
-            hipLaunchKernelGGL((k_merge_slots<R>), dim3(mgrid), dim3(256), 0, c->stream,
-                               (typename V2<R>::T*)b.slots, b.subs, b.nsub, b.tsub, (int)LL, level);
+        hipLaunchKernelGGL((k_merge_slots<R>), dim3(mgrid), dim3(kMergeThreads), 0, c->stream,
+                           (typename V2<R>::T*)b.slots, b.subs, b.nsub, b.tsub, (int)LL);
         FH_HIP(hipGetLastError());
     }
     return FH_OK;
@@ -2777,9 +2795,9 @@ fh_status reduce_grid(fh_ctx* c, int ninst, const GridGeom& gg, const SpreadBufs
 template <class R>
 fh_status run_spread(fh_ctx* c, const InstParams& p0, const InstParams* table, int ninst, int64_t Ntot,
                      const GridGeom& gg, const SpreadBufs& b, R* F, double beta, const void* poly,
-                     const int2* rwin = nullptr, int64_t total_rows = -1)
+                     const int2* rwin = nullptr, int64_t total_rows = -1, const RowFactors& rf = RowFactors{})
 {
-    FH_TRY(spread_items<R>(c, p0, table, ninst, Ntot, gg, b, beta, poly));
+    FH_TRY(spread_items<R>(c, p0, table, ninst, Ntot, gg, b, beta, poly, rf));
     return reduce_grid<R>(c, ninst, gg, b, F, rwin, total_rows);
 }
 
