@@ -353,6 +353,12 @@ fh_status device_bbox2(fh_ctx* c, const double* x1, const double* y1, int64_t n1
 void timing_mark(fh_ctx* c, int i);
 void timing_finish(fh_ctx* c);
 
+// The quadrature sum of a small grid call as it stands (fh_direct.hip):
+// whether it serves the call, and the call (u null: the output goes to
+// extra_bytes of workspace returned in *extra).
+bool direct_serves(const fh_ctx* c, const fh_quad* q, int n1, int n2);
+fh_status t1_direct(fh_ctx* c, const fh_quad* q, double lambda, double z, int n1, int n2, double h1, double h2,
+                    double xc, double yc, int occ, void* u, size_t extra_bytes, void** extra);
 // Device table of the nf roots exp(-2 pi i m/nf), m < nf (complex double).
 fh_status roots_table(fh_ctx* c, int nf, const double2** dev);
 

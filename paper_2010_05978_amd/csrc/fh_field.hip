@@ -372,11 +372,20 @@ fh_status t1_pipeline(fh_ctx* c, int B, const fh_quad* const* qs, const double* 
     FH_ARG(Ntot < ((int64_t)1 << 31), FH_ERR_UNSUPPORTED, "%lld nodes in one call; at most 2^31 - 1",
            (long long)Ntot);
     if (!rebuild) {
+        // either path's workspace may not fit where the tiled path's does
+        // (a capped context): the call then goes on to that
+        if (B == 1 && direct_serves(c, qs[0], n1, n2)) {
+            const fh_status s =
+                t1_direct(c, qs[0], lambda[0], z[0], n1, n2, h1, h2, xc, yc, occ[0], u, extra_bytes, extra);
+            if (s != FH_ERR_ALLOC) return s;
+        }
         std::vector<InstParams> winst(inst);
         WinGeom wg;
         fh_status ws;
-        if (window_plan<R>(c, pl, B, qs, winst, Ntot, wg, ws))
-            return t1_window<R>(c, pl, wg, B, winst, epi, n1, n2, h1, h2, xc, yc, u, extra_bytes, extra);
+        if (window_plan<R>(c, pl, B, qs, winst, Ntot, wg, ws)) {
+            const fh_status s = t1_window<R>(c, pl, wg, B, winst, epi, n1, n2, h1, h2, xc, yc, u, extra_bytes, extra);
+            if (s != FH_ERR_ALLOC) return s;
+        }
         FH_TRY(ws);
     }
     size_items(c, gg, Ntot);
