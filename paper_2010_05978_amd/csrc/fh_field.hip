@@ -206,6 +206,39 @@ bool reach_cells(double lo, double hi, double s, int W, int nf, int& first, int&
     return true;
 }
 
+// Workgroups per instance of the window spread: as many as are resident at
+// once, at least two batches of 64 nodes per wavefront.
+template <class R>
+int win_blocks(const fh_ctx* c, int SX, int SY, int W, int B, int64_t Ntot)
+{
+    const int64_t per_cu = std::min<int64_t>(4, kCuLds / win_lds(SX, SY, W, sizeof(R)));
+    const int64_t resident = std::max<int64_t>(1, c->cu_count * per_cu / B);
+    const int64_t enough = (Ntot / B + 128 * kWinWaves - 1) / (128 * kWinWaves);
+    return (int)std::max<int64_t>(1, std::min(resident, enough));
+}
+
+template <class R>
+fh_status launch_win_spread(fh_ctx* c, int W, int B, const InstParams& p0, const InstParams* table, const WinGeom& wg,
+                            typename V2<R>::T* part, const void* poly)
+{
+    const size_t lds = win_lds(wg.SX, wg.SY, W, sizeof(R));
+    const dim3 grid(wg.nblk, B);
+    switch (W) {
+#define FH_WIN_CASE(w)                                                                                        \
+    case w:                                                                                                   \
+        hipLaunchKernelGGL((k_win_spread<R, w>), grid, dim3(64 * kWinWaves), lds, c->stream, p0, table, wg,   \
+                           part, (const R*)poly);                                                             \
+        break;
+        FH_WIN_CASE(2) FH_WIN_CASE(3) FH_WIN_CASE(4) FH_WIN_CASE(5) FH_WIN_CASE(6) FH_WIN_CASE(7) FH_WIN_CASE(8)
+        FH_WIN_CASE(9) FH_WIN_CASE(10) FH_WIN_CASE(11) FH_WIN_CASE(12) FH_WIN_CASE(13) FH_WIN_CASE(14)
+        FH_WIN_CASE(15) FH_WIN_CASE(16)
+#undef FH_WIN_CASE
+    default: set_error("kernel width %d unsupported", W); return FH_ERR_UNSUPPORTED;
+    }
+    FH_HIP(hipGetLastError());
+    return FH_OK;
+}
+
 // Whether the window path (fh_window.hpp) takes the call, and its geometry.
 // Its window or windows must fit a workgroup's 64 KB of LDS with the staging,
 // which bounds it at some 47 x 47 cells in FP64 and 39 x 39 in FP32 (more
@@ -248,12 +281,7 @@ bool window_plan(fh_ctx* c, const T1Plan& pl, int B, const fh_quad* const* qs, s
     wg.SX = SX;
     wg.SY = SY;
     if (win_dft_lds(SX, (SY + 15) / 16, 16, sizeof(R)) > kLdsBudget) return false;
-    // workgroups: as many as are resident at once, at least two batches of
-    // 64 nodes per wavefront
-    const int64_t per_cu = std::min<int64_t>(4, kCuLds / (win_lds(SX, SY, pl.k.w, sizeof(R))));
-    const int64_t resident = std::max<int64_t>(1, c->cu_count * per_cu / B);
-    const int64_t enough = (Ntot / B + 128 * kWinWaves - 1) / (128 * kWinWaves);
-    wg.nblk = (int)std::max<int64_t>(1, std::min(resident, enough));
+    wg.nblk = win_blocks<R>(c, SX, SY, pl.k.w, B, Ntot);
     return true;
 }
 
@@ -294,19 +322,10 @@ fh_status t1_window(fh_ctx* c, const T1Plan& pl, const WinGeom& wg, int B, const
     const EpiInst* etab = B > 1 ? depi : nullptr;
     timing_mark(c, 0);
     timing_mark(c, 1);
-    const size_t slds = win_lds(wg.SX, wg.SY, W, sizeof(R));
-    const dim3 sgrid(wg.nblk, B);
-    switch (W) {
-#define FH_WIN_CASE(w)                                                                                           case w:                                                                                                          hipLaunchKernelGGL((k_win_spread<R, w>), sgrid, dim3(64 * kWinWaves), slds, c->stream, inst[0], tab,                            wg, part, (const R*)pl.k.poly);                                                           break;
-        FH_WIN_CASE(2) FH_WIN_CASE(3) FH_WIN_CASE(4) FH_WIN_CASE(5) FH_WIN_CASE(6) FH_WIN_CASE(7) FH_WIN_CASE(8)
-        FH_WIN_CASE(9) FH_WIN_CASE(10) FH_WIN_CASE(11) FH_WIN_CASE(12) FH_WIN_CASE(13) FH_WIN_CASE(14)
-        FH_WIN_CASE(15) FH_WIN_CASE(16)
-#undef FH_WIN_CASE
-    default: set_error("kernel width %d unsupported", W); return FH_ERR_UNSUPPORTED;
-    }
+    FH_TRY(launch_win_spread<R>(c, W, B, inst[0], tab, wg, part, pl.k.poly));
     timing_mark(c, 2);
-    hipLaunchKernelGGL((k_win_sum<R>), dim3(nblocks(cells, 16), B), dim3(256), 0, c->stream, (const C2*)part, cells,
-                       wg.nblk, G);
+    hipLaunchKernelGGL((k_win_sum<R, false>), dim3(nblocks(cells, 16), B), dim3(256), 0, c->stream,
+                       (const C2*)part, wg, G);
     timing_mark(c, 3);
     // output rows per workgroup: up to 128, fewer while that leaves fewer
     // than two workgroups per CU (each repeats the columns' sum, which costs
@@ -715,16 +734,30 @@ fh_status t3_core(fh_ctx* c, const fh_quad* q, double lambda, double z, int64_t 
     LdsCols lcol = lds_cols_plan(c, d2.m, d1.m, rs);
     const bool lds2d = lr.C > 0 && lcol.C > 0;
     if (!lds2d) FH_TRY(fft_plan(c, d1.m, d2.m, 1, &fp));
-    FH_TRY(counters_ready(c, ntiles));
+    // A grid that a workgroup's LDS holds (up to 48 x 48 cells in FP64) is
+    // one window: the window spread takes a generated rule without binning,
+    // slots and their merge (as window_plan, which gives the conditions; a
+    // node's stencil never leaves the grid, which is planned that wide).
+    // 998,400 nodes of a starshade on a 32 x 32 grid, 1e4 targets: FP64 at 1e-9
+    // 176 -> 82 us, at 1e-12 242 -> 90, mixed 107 -> 52; 1e6 targets 281 -> 187.
+    const fh_options& op = c->opt;
+    const bool window = op.spread_method == 0 && op.tile == 0 && op.max_subproblem == 0 && !op.deterministic &&
+                        k.w <= 16 && k.poly && !q->user_nodes &&
+                        win_lds(d1.nf, d2.nf, k.w, rs) <= kLdsBudget;
+    WinGeom wg{d1.nf, d2.nf, d1.nf, d2.nf, 1};
+    if (window) wg.nblk = win_blocks<R>(c, d1.nf, d2.nf, k.w, 1, N);
+    if (!window) FH_TRY(counters_ready(c, ntiles));
     const size_t fine_count = 2 * (size_t)d1.nf * d2.nf;
     const size_t up_count = 2 * (size_t)d1.m * d2.m;
     const size_t need = aligned_bytes(rs * fine_count) + aligned_bytes(rs * up_count) +
-                        spread_bytes(c, N, gg, ntiles, rs) + (host ? 2 * cbytes : 0) +
-                        (stage_out ? obytes : 0);
+                        (window ? aligned_bytes(rs * fine_count * wg.nblk) : spread_bytes(c, N, gg, ntiles, rs)) +
+                        (host ? 2 * cbytes : 0) + (stage_out ? obytes : 0);
     FH_TRY(arena_reserve(c, need));
     R* fine = c->arena.take<R>(fine_count);
     R* up = c->arena.take<R>(up_count);
-    SpreadBufs sbuf = spread_carve(c, N, gg, ntiles, rs);
+    R* part = window ? c->arena.take<R>(fine_count * wg.nblk) : nullptr;
+    SpreadBufs sbuf{};
+    if (!window) sbuf = spread_carve(c, N, gg, ntiles, rs);
     const double* dxi = xi;
     const double* deta = eta;
     if (host) {
@@ -774,7 +807,19 @@ fh_status t3_core(fh_ctx* c, const fh_quad* q, double lambda, double z, int64_t 
     tp.ch2 = inv_phi_cheb_cached(c, k, d2.theta_max);
 
     timing_mark(c, 0);
-    FH_TRY(run_spread<R>(c, ip, nullptr, 1, N, gg, sbuf, fine, k.beta, k.poly));
+    if (window) {
+        using C2 = typename V2<R>::T;
+        ip.sh1 = -(d1.nf / 2);
+        ip.sh2 = -(d2.nf / 2);
+        timing_mark(c, 1);
+        FH_TRY(launch_win_spread<R>(c, k.w, 1, ip, nullptr, wg, reinterpret_cast<C2*>(part), k.poly));
+        timing_mark(c, 2);
+        hipLaunchKernelGGL((k_win_sum<R, true>), dim3(nblocks((int64_t)d1.nf * d2.nf, 16)), dim3(256), 0, c->stream,
+                           reinterpret_cast<const C2*>(part), wg, reinterpret_cast<C2*>(fine));
+        FH_HIP(hipGetLastError());
+    } else {
+        FH_TRY(run_spread<R>(c, ip, nullptr, 1, N, gg, sbuf, fine, k.beta, k.poly));
+    }
     if (lds2d) {
         const int gr = (d2.m + lr.C - 1) / lr.C, gc = (d1.m + lcol.C - 1) / lcol.C;
         FH_LDS_LAUNCH(k_t3_rows, R, lr, dim3(xcd_blocks(gr)), c->stream, fine, d1.nf, d2.nf, up, d1.m, d2.m, lr.C,

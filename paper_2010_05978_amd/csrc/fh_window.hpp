@@ -1,4 +1,4 @@
-// fh_window.hpp -- type 1 for rules whose nodes reach a few fine-grid cells.
+// fh_window.hpp -- rules whose nodes reach a few fine-grid cells.
 //
 // A large occulter seen on a fine pupil grid (a 24 m starshade, h = 2.3 mm)
 // puts a million nodes into a window of some 26 x 26 cells of the fine grid.
@@ -12,6 +12,7 @@
 //   k_win_sum     adds the workgroups' windows in a fixed order;
 //   k_win_dft     the window's Fourier sums at the n1 x n2 outputs as two
 //                 matrix products (columns, then rows), with the epilogue.
+// Type 3 seen from a small pupil has as small a grid, and takes the first two.
 #pragma once
 #include "fh_kernels.hpp"
 
@@ -238,11 +239,14 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
 }
 
 // G[b] = the sum of instance b's nblk windows: 16 cells per workgroup, 16
-// threads a cell, each over every 16th window, then in thread order.
-template <class R>
-__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part, int cells, int nblk,
+// threads a cell, each over every 16th window, then in thread order.  WRAP:
+// the window is a whole periodic grid from its cell (-nf1/2, -nf2/2) on (type
+// 3), and each sum goes to its place in the period.
+template <class R, bool WRAP>
+__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part, WinGeom wg,
                                                  typename V2<R>::T* __restrict__ G)
 {
+    const int cells = wg.SX * wg.SY, nblk = wg.nblk;
     using C = typename V2<R>::T;
     __shared__ C s[16][17];
     const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4, b = blockIdx.y;
@@ -264,7 +268,13 @@ __global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __rest
         a.x += s[i][threadIdx.x].x;
         a.y += s[i][threadIdx.x].y;
     }
-    G[(size_t)b * cells + e] = a;
+    if constexpr (WRAP) {
+        const int r = e / wg.SX, c = e - r * wg.SX;
+        const int y = r - wg.nf2 / 2, x = c - wg.nf1 / 2;
+        G[(size_t)(y < 0 ? y + wg.nf2 : y) * wg.nf1 + (x < 0 ? x + wg.nf1 : x)] = a;
+    } else {
+        G[(size_t)b * cells + e] = a;
+    }
 }
 
 // LDS of k_win_dft: the window with its columns padded to a multiple of 4
