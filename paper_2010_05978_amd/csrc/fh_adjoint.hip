@@ -595,14 +595,22 @@ __global__ void __launch_bounds__(128) k_ss_vjp_partial(SsParams sp, int s0, con
     }
 }
 
-// g_coef[2 k K + j] = sum over chunks (fixed order).
+// g_coef[2 k K + j] = sum over chunks (fixed order; a thread per coefficient
+// waits for memory only, so sixteen chunks are loaded at a time).
 __global__ void k_ss_vjp_final(SsParams sp, const double* __restrict__ part, double* __restrict__ gcoef)
 {
     const int o = blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= sp.Np * 2 * sp.K) return;
     const int k = o / (2 * sp.K), jj = o - k * 2 * sp.K;
+    const double* __restrict__ p = part + (int64_t)k * sp.nchunks * 2 * sp.K + jj;
     double acc = 0.0;
-    for (int ch = 0; ch < sp.nchunks; ++ch) acc += part[((int64_t)k * sp.nchunks + ch) * 2 * sp.K + jj];
+    for (int ch = 0; ch < sp.nchunks; ch += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = ch + u < sp.nchunks ? p[(int64_t)(ch + u) * 2 * sp.K] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += v[u];
+    }
     gcoef[o] = acc;
 }
 

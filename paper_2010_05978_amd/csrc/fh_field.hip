@@ -310,13 +310,18 @@ fh_status t1_window(fh_ctx* c, const T1Plan& pl, const WinGeom& wg, int B, const
                                 aligned_bytes(extra_bytes)));
     C2* part = c->arena.take<C2>(nwin * cells);
     C2* G = c->arena.take<C2>((size_t)B * cells);
-    InstParams* dinst = c->arena.take<InstParams>(B);
-    EpiInst* depi = c->arena.take<EpiInst>(B);
+    // both tables in one copy (each copy of host memory costs a launch)
+    const size_t ib = aligned_bytes(sizeof(InstParams) * B), eb = sizeof(EpiInst) * B;
+    char* dtab = c->arena.take<char>(ib + eb);
+    InstParams* dinst = reinterpret_cast<InstParams*>(dtab);
+    EpiInst* depi = reinterpret_cast<EpiInst*>(dtab + ib);
     if (extra) *extra = c->arena.take<char>(extra_bytes);
     if (!u) u = static_cast<R*>(*extra);
     if (B > 1) {
-        FH_HIP(hipMemcpyAsync(dinst, inst.data(), sizeof(InstParams) * B, hipMemcpyHostToDevice, c->stream));
-        FH_HIP(hipMemcpyAsync(depi, epi.data(), sizeof(EpiInst) * B, hipMemcpyHostToDevice, c->stream));
+        std::vector<char> tab(ib + eb);
+        std::memcpy(tab.data(), inst.data(), sizeof(InstParams) * B);
+        std::memcpy(tab.data() + ib, epi.data(), eb);
+        FH_HIP(hipMemcpyAsync(dtab, tab.data(), ib + eb, hipMemcpyHostToDevice, c->stream));
     }
     const InstParams* tab = B > 1 ? dinst : nullptr;
     const EpiInst* etab = B > 1 ? depi : nullptr;
