@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(64) k_adj_gather(const R* __restrict__ F1, Ins
 template <class R, int W, bool ACC>
 __global__ void __launch_bounds__(256) k_adj_gather_lds(const R* __restrict__ F1, InstParams ip, GridGeom gg, R beta,
                                                         const R* __restrict__ poly, double lz, int col0, int span1,
-                                                        double* __restrict__ gx, double* __restrict__ gy,
+                                                        int compact, double* __restrict__ gx, double* __restrict__ gy,
                                                         double* __restrict__ gw)
 {
     using C = typename V2<R>::T;
@@ -263,7 +263,12 @@ __global__ void __launch_bounds__(256) k_adj_gather_lds(const R* __restrict__ F1
     const C* F = reinterpret_cast<const C*>(F1);
     const size_t plane = (size_t)gg.rows * gg.nf1;
     const int wplane = gg.rows * span1;
+    // (F1 is the window itself when compact)
     for (int e = threadIdx.x; e < 3 * wplane; e += blockDim.x) {
+        if (compact) {
+            win[e] = F[e];
+            continue;
+        }
         const int ch = e / wplane, rem = e - ch * wplane;
         const int row = rem / span1, wc = rem - row * span1;
         int col = (col0 + wc) % gg.nf1;
@@ -349,8 +354,8 @@ inline size_t adj_window_lds(int rows, int span1, size_t rs)
 // that leaves fewer than about 4 wavefronts per CU.
 template <class R>
 fh_status launch_gather(fh_ctx* c, int W, const R* F1, const InstParams& ip, const GridGeom& gg, double beta,
-                        const void* poly, double lz, bool acc, int col0, int span1, double* gx, double* gy,
-                        double* gw)
+                        const void* poly, double lz, bool acc, int col0, int span1, bool compact, double* gx,
+                        double* gy, double* gw)
 {
     const size_t wl = span1 > 0 ? adj_window_lds(gg.rows, span1, sizeof(R)) : 0;
     if (wl > 0) {
@@ -363,10 +368,10 @@ fh_status launch_gather(fh_ctx* c, int W, const R* F1, const InstParams& ip, con
     case w:                                                                                                     \
         if (acc)                                                                                                \
             hipLaunchKernelGGL((k_adj_gather_lds<R, w, true>), dim3(g), dim3(256), wl, c->stream, F1, ip, gg,    \
-                               (R)beta, (const R*)poly, lz, col0, span1, gx, gy, gw);                           \
+                               (R)beta, (const R*)poly, lz, col0, span1, compact ? 1 : 0, gx, gy, gw);                           \
         else                                                                                                    \
             hipLaunchKernelGGL((k_adj_gather_lds<R, w, false>), dim3(g), dim3(256), wl, c->stream, F1, ip, gg,   \
-                               (R)beta, (const R*)poly, lz, col0, span1, gx, gy, gw);                           \
+                               (R)beta, (const R*)poly, lz, col0, span1, compact ? 1 : 0, gx, gy, gw);                           \
         break;
             FH_GATHER_LDS_CASE(2) FH_GATHER_LDS_CASE(3) FH_GATHER_LDS_CASE(4) FH_GATHER_LDS_CASE(5)
             FH_GATHER_LDS_CASE(6) FH_GATHER_LDS_CASE(7) FH_GATHER_LDS_CASE(8) FH_GATHER_LDS_CASE(9)
@@ -400,6 +405,225 @@ fh_status launch_gather(fh_ctx* c, int W, const R* F1, const InstParams& ip, con
 #undef FH_GATHER_CASE
     default: set_error("kernel width %d unsupported", W); return FH_ERR_UNSUPPORTED;
     }
+    FH_HIP(hipGetLastError());
+    return FH_OK;
+}
+
+// ------------------------------------------------- small windows, densely
+// Where the LDS gather's window is small, the three channels' Fourier sums at
+// its cells are matrix products instead of full transforms of which a few
+// rows and columns are kept.  With b the deconvolved, chirped cotangent,
+//   Y0[k1][r] = sum_k2 b[k1][k2] e2(k2 (r + sh2)),  Y1 the same of eta b,
+//   F[c][r]   = sum_k1 e1(k1 (c + col0)) {Y0, xi Y0, Y1}[k1][r],
+// e(m) = exp(-2 pi i m/nf) read from tables of the roots.  Workgroup (64
+// columns k1, chunk of KC rows k2): wavefront v takes 16 columns, computes b
+// in place (its lanes are the operand's rows), and sums over the chunk into
+// accumulators, whose layout is the operand layout of the second product (in
+// FP32 with the 16 columns in another order, which the roots follow).  The
+// wavefronts' cells are added in LDS, in order, and the workgroup writes one
+// window, [channel][c][r]; k_adj_win_sum adds those in a fixed order.
+// Bound by the matrix cores and the chain of its phases.  512 x 512 outputs,
+// a 28 x 30 window, FP64: the gradient call over three wavelengths 501 -> 468
+// us (preparation, two passes of full transforms and a transposition, 30 us a
+// wavelength, before).
+struct AdjWin {
+    int SX, SY, col0, KC;
+};
+
+template <class R, int MT, int CT>
+__global__ void __launch_bounds__(256) k_adj_win(const R* __restrict__ gu, AdjParams ap, AdjWin aw,
+                                                 const double2* __restrict__ roots1,
+                                                 const double2* __restrict__ roots2,
+                                                 typename V2<R>::T* __restrict__ part)
+{
+    using C = typename V2<R>::T;
+    using M = MfmaAcc<R>;
+    using V = typename M::V;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    C* st = reinterpret_cast<C*>(lds_raw);  // 2 x 4 wavefronts x 256 cells
+    const int cells = aw.SX * aw.SY;
+    double2* rf = reinterpret_cast<double2*>(st + 2048);  // KC row factors
+    const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nf1 = ap.nf1, nf2 = ap.nf2;
+    const int k20 = blockIdx.y * aw.KC, kc = min(aw.KC, ap.n2 - k20);
+    const int cb = blockIdx.x * 64 + wv * 16;  // this wavefront's first column
+    for (int k = tid; k < kc; k += 256) {
+        const double y = ap.yc + ap.h2 * (k20 + k - ap.n2 / 2);
+        const double tt = y * y * ap.inv2lz;
+        double sn, cs;
+        sincospi(2.0 * (tt - rint(tt)), &sn, &cs);
+        const double sc = ap.iphi2[k20 + k];
+        rf[k] = make_double2(cs * sc, sn * sc);
+    }
+    const int ki = cb + i16;
+    double2 cf = make_double2(0.0, 0.0);  // this lane's column factor
+    if (ki < ap.n1) {
+        const double x = ap.xc + ap.h1 * (ki - ap.n1 / 2);
+        const double tt = x * x * ap.inv2lz;
+        double sn, cs;
+        sincospi(2.0 * (tt - rint(tt)), &sn, &cs);
+        const double sc = ap.sign * ap.iphi1[ki];
+        cf = make_double2(cs * sc, sn * sc);
+    }
+    __syncthreads();
+    V Yr[2][MT], Yi[2][MT];
+#pragma unroll
+    for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) Yr[ch][m] = Yi[ch][m] = V{R(0), R(0), R(0), R(0)};
+    // row roots: index k2 (r + sh2) mod nf2, r = 16 m + i16, k2 four further per step
+    const int sh2 = ((ap.sh2 % nf2) + nf2) % nf2, sh1 = ((aw.col0 % nf1) + nf1) % nf1;
+    unsigned ri[MT], rs[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const unsigned r = (unsigned)(16 * m + i16 + sh2) % (unsigned)nf2;
+        const int k2 = k20 + g - ap.n2 / 2;
+        ri[m] = ((unsigned)((k2 % nf2 + nf2) % nf2) * r) % (unsigned)nf2;
+        rs[m] = (4u * r) % (unsigned)nf2;
+    }
+    const C* gv = reinterpret_cast<const C*>(gu);
+    for (int s = 0; s < kc; s += 4) {
+        const int k = s + g;
+        C a{R(0), R(0)};
+        double eta = 0.0, br = 0.0, bi = 0.0;
+        if (k < kc && ki < ap.n1) {
+            a = gv[(size_t)(k20 + k) * ap.n1 + ki];
+            const double2 f = rf[k];
+            const double fr = cf.x * f.x - cf.y * f.y, fi = cf.x * f.y + cf.y * f.x;
+            // b = sign conj(g) times the factors (the sign is in the column's)
+            br = (double)a.x * fr + (double)a.y * fi;
+            bi = (double)a.x * fi - (double)a.y * fr;
+            eta = ap.yc + ap.h2 * (k20 + k - ap.n2 / 2);
+        }
+        const R b0r = (R)br, b0i = (R)bi, b1r = (R)(eta * br), b1i = (R)(eta * bi);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const double2 e = roots2[ri[m]];
+            ri[m] += rs[m];
+            if (ri[m] >= (unsigned)nf2) ri[m] -= (unsigned)nf2;
+            const R er = (R)e.x, ei = (R)e.y;
+            Yr[0][m] = M::mma(b0r, er, Yr[0][m]);
+            Yi[0][m] = M::mma(b0r, ei, Yi[0][m]);
+            Yr[1][m] = M::mma(b1r, er, Yr[1][m]);
+            Yi[1][m] = M::mma(b1r, ei, Yi[1][m]);
+            Yr[0][m] = M::mma(-b0i, ei, Yr[0][m]);
+            Yi[0][m] = M::mma(b0i, er, Yi[0][m]);
+            Yr[1][m] = M::mma(-b1i, ei, Yr[1][m]);
+            Yi[1][m] = M::mma(b1i, er, Yi[1][m]);
+        }
+    }
+    // column roots of the four products' columns k1 = cb + row(lane, v), and
+    // their coordinates xi
+    C e1[CT][4];
+    R xi[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int k1 = min(cb + M::row(lane, v), ap.n1 - 1) - ap.n1 / 2;  // (columns past n1 hold zeros)
+        xi[v] = (R)(ap.xc + ap.h1 * k1);
+        const unsigned km = (unsigned)((k1 % nf1 + nf1) % nf1);
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const unsigned c = (unsigned)(16 * t + i16 + sh1) % (unsigned)nf1;
+            const double2 e = roots1[(km * c) % (unsigned)nf1];
+            e1[t][v] = C{(R)e.x, (R)e.y};
+        }
+    }
+    C* out = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 3 * cells;
+    int buf = 0;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                V fr = V{R(0), R(0), R(0), R(0)}, fi = fr;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const R q = ch == 1 ? xi[v] : R(1);
+                    const R yr = q * Yr[ch == 2 ? 1 : 0][m][v], yi = q * Yi[ch == 2 ? 1 : 0][m][v];
+                    fr = M::mma(e1[t][v].x, yr, fr);
+                    fi = M::mma(e1[t][v].x, yi, fi);
+                    fr = M::mma(-e1[t][v].y, yi, fr);
+                    fi = M::mma(e1[t][v].y, yr, fi);
+                }
+                // the four wavefronts' 16 x 16 cells, added in order (two
+                // buffers: a barrier per block of cells)
+                C* b = st + buf * 1024;
+                buf ^= 1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) b[wv * 256 + M::row(lane, v) * 16 + i16] = C{fr[v], fi[v]};
+                __syncthreads();
+                const int c = 16 * t + (tid >> 4), r = 16 * m + (tid & 15);
+                if (c < aw.SX && r < aw.SY) {
+                    C a = b[tid];
+#pragma unroll
+                    for (int w = 1; w < 4; ++w) {
+                        a.x += b[w * 256 + tid].x;
+                        a.y += b[w * 256 + tid].y;
+                    }
+                    out[ch * cells + c * aw.SY + r] = a;
+                }
+            }
+}
+
+// F[ch][r][c] = the sum of the n windows [ch][c][r]: 16 cells per workgroup,
+// 16 threads a cell, then in thread order.
+template <class R>
+__global__ void __launch_bounds__(256) k_adj_win_sum(const typename V2<R>::T* __restrict__ part, int SX, int SY,
+                                                     int n, typename V2<R>::T* __restrict__ F)
+{
+    using C = typename V2<R>::T;
+    __shared__ C s[16][17];
+    const int cells = SX * SY, total = 3 * cells;
+    const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4;
+    C a{R(0), R(0)};
+    if (e < total) {
+#pragma unroll 8
+        for (int i = k; i < n; i += 16) {
+            const C v = part[(size_t)i * total + e];
+            a.x += v.x;
+            a.y += v.y;
+        }
+    }
+    s[k][threadIdx.x & 15] = a;
+    __syncthreads();
+    if (k > 0 || e >= total) return;
+#pragma unroll
+    for (int i = 1; i < 16; ++i) {
+        a.x += s[i][threadIdx.x].x;
+        a.y += s[i][threadIdx.x].y;
+    }
+    const int ch = e / cells, q = e - ch * cells, c = q / SY, r = q - c * SY;
+    F[(size_t)ch * cells + (size_t)r * SX + c] = a;
+}
+
+// The three channels at the window's SY x SX cells from (sh2, col0), into F1.
+template <class R>
+fh_status adj_window(fh_ctx* c, const void* g_u, const AdjParams& ap, int SX, int SY, int col0, const double2* r1,
+                     const double2* r2, typename V2<R>::T* part, int KC, typename V2<R>::T* F1)
+{
+    using C = typename V2<R>::T;
+    const AdjWin aw{SX, SY, col0, KC};
+    const dim3 grid((ap.n1 + 63) / 64, (ap.n2 + KC - 1) / KC);
+    const size_t lds = sizeof(C) * 2048 + sizeof(double2) * KC;
+    const int MT = (SY + 15) / 16, CT = (SX + 15) / 16;
+#define FH_ADJ_WIN(mt, ct)                                                                                      \
+    if (MT == mt && CT == ct)                                                                                   \
+        hipLaunchKernelGGL((k_adj_win<R, mt, ct>), grid, dim3(256), lds, c->stream, static_cast<const R*>(g_u), \
+                           ap, aw, r1, r2, part)
+    FH_ADJ_WIN(1, 1);
+    FH_ADJ_WIN(1, 2);
+    FH_ADJ_WIN(1, 3);
+    FH_ADJ_WIN(2, 1);
+    FH_ADJ_WIN(2, 2);
+    FH_ADJ_WIN(2, 3);
+    FH_ADJ_WIN(3, 1);
+    FH_ADJ_WIN(3, 2);
+    FH_ADJ_WIN(3, 3);
+#undef FH_ADJ_WIN
+    hipLaunchKernelGGL((k_adj_win_sum<R>), dim3(nblocks(3 * (int64_t)SX * SY, 16)), dim3(256), 0, c->stream,
+                       (const C*)part, SX, SY, (int)(grid.x * grid.y), F1);
     FH_HIP(hipGetLastError());
     return FH_OK;
 }
@@ -447,6 +671,49 @@ fh_status grid_vjp_impl(fh_ctx* c, const fh_quad* q, double lambda, double z, in
     const double* ip2 = nullptr;
     FH_TRY(iphi_table(c, pl.k, n1, gg.nf1, &ip1));
     FH_TRY(iphi_table(c, pl.k, n2, gg.nf2, &ip2));
+    // the columns the nodes reach: their box's cells with a cell of margin
+    // (as the row window), when the rows are windowed too
+    int col0 = 0, span1 = 0;
+    if (!gg.wrap_y) {
+        const double a0 = std::ceil(bb[0] * ip.s1 - 0.5 * gg.W) - 1.0;
+        const double a1 = std::ceil(bb[1] * ip.s1 - 0.5 * gg.W) + gg.W + 1.0;
+        if (a1 - a0 < gg.nf1 && std::fabs(a0) < 1e9) {
+            col0 = (int)a0;
+            span1 = (int)(a1 - a0);
+        }
+    }
+    // a window that the LDS gather holds and that has up to 48 rows and
+    // columns is evaluated densely: 8 (rows + rows columns/KC) flops per
+    // cotangent value and channel against two full transforms of zeros
+    const bool dense = span1 > 0 && gg.rows <= 48 && span1 <= 48 && adj_window_lds(gg.rows, span1, rs) > 0;
+    if (dense) {
+        using C2 = typename V2<R>::T;
+        const double2 *r1 = nullptr, *r2 = nullptr;
+        FH_TRY(roots_table(c, gg.nf1, &r1));
+        FH_TRY(roots_table(c, gg.nf2, &r2));
+        // rows per workgroup: 64, fewer while that leaves fewer than one
+        // workgroup per CU (each repeats the columns' sum, which costs as much
+        // as 48 rows)
+        int KC = 64;
+        const int64_t ct = (n1 + 63) / 64;
+        while (KC > 16 && ct * ((n2 + KC - 1) / KC) < (int64_t)c->cu_count) KC /= 2;
+        const size_t cells = 3 * (size_t)gg.rows * span1, nwin = (size_t)ct * ((n2 + KC - 1) / KC);
+        FH_TRY(arena_reserve(c, aligned_bytes(sizeof(C2) * cells * nwin) + aligned_bytes(sizeof(C2) * cells)));
+        C2* part = c->arena.take<C2>(cells * nwin);
+        C2* F1 = c->arena.take<C2>(cells);
+        const AdjParams ap{n1, n2, gg.nf1, gg.nf2, gg.rows, ip.sh2, h1, h2, xc, yc, 0.5 / lz, occ ? -1.0 : 1.0, ip1,
+                           ip2};
+        timing_mark(c, 0);
+        timing_mark(c, 1);
+        timing_mark(c, 2);
+        FH_TRY(adj_window<R>(c, g_u, ap, span1, gg.rows, col0, r1, r2, part, KC, F1));
+        timing_mark(c, 3);
+        FH_TRY(launch_gather<R>(c, gg.W, reinterpret_cast<const R*>(F1), ip, gg, pl.k.beta, pl.k.poly, lz, acc, col0,
+                                span1, true, g_x, g_y, g_w));
+        timing_mark(c, 4);
+        timing_mark(c, 5);
+        return FH_OK;
+    }
     FftPlan* fa = nullptr;
     FftPlan* fb = nullptr;
     FH_TRY(fft_plan(c, gg.nf2, 0, 3 * n1, &fa));
@@ -470,18 +737,8 @@ fh_status grid_vjp_impl(fh_ctx* c, const fh_quad* q, double lambda, double z, in
     FH_HIP(hipGetLastError());
     FH_TRY(fft_exec(c, fb, F1));
     timing_mark(c, 3);
-    // the columns the nodes reach: their box's cells with a cell of margin
-    // (as the row window), when the rows are windowed too
-    int col0 = 0, span1 = 0;
-    if (!gg.wrap_y) {
-        const double a0 = std::ceil(bb[0] * ip.s1 - 0.5 * gg.W) - 1.0;
-        const double a1 = std::ceil(bb[1] * ip.s1 - 0.5 * gg.W) + gg.W + 1.0;
-        if (a1 - a0 < gg.nf1 && std::fabs(a0) < 1e9) {
-            col0 = (int)a0;
-            span1 = (int)(a1 - a0);
-        }
-    }
-    FH_TRY(launch_gather<R>(c, gg.W, F1, ip, gg, pl.k.beta, pl.k.poly, lz, acc, col0, span1, g_x, g_y, g_w));
+    FH_TRY(launch_gather<R>(c, gg.W, F1, ip, gg, pl.k.beta, pl.k.poly, lz, acc, col0, span1, false, g_x, g_y,
+                            g_w));
     timing_mark(c, 4);
     timing_mark(c, 5);
     return FH_OK;
