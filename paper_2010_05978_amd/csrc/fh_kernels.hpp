@@ -2982,10 +2982,18 @@ T1Plan plan_t1(fh_ctx* c, int n1, int n2, int64_t N)
         g.ntx = g.nf1 / T;
         g.nty = g.nf2 / T;
         g.padx = g.pady = 0;
-        // a 16-cell tile's padded tile takes 2 x 2 blocks of matrix-core
-        // products, four times the work: the chosen spread becomes the
-        // wavefront spread unless the caller asked for this one
-        if (c->opt.spread_method <= 0) method = 2;
+        // A 16-cell tile's padded tile takes 2 x 2 blocks of matrix-core
+        // products, four times the work of one.  In FP64 it is only the
+        // 10- and 11-cell kernels that come here (wider tiles follow), whose
+        // products still beat the wavefront spread's adds to LDS: 100 rules
+        // of 10k to 400k nodes on 256 x 256 grids take 2.70 ms for 3.01 ms,
+        // one of 900k nodes on 1000 x 1000 209 us for 221 us, and where the
+        // nodes crowd into few tiles the two are equal.  In FP32, where
+        // only a kernel width of the caller's leads here, the adds cost half
+        // (7-cell kernels on 16-cell tiles, that batch: 1.03 ms for 1.48 ms)
+        // and the chosen spread becomes the wavefront spread unless the
+        // caller asked for this one.
+        if (c->opt.spread_method <= 0 && c->prec != FH_FP64) method = 2;
     }
     spread_defaults(c, g, method);
     return p;
