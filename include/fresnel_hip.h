@@ -72,7 +72,12 @@ typedef struct fh_targets fh_targets;
  * automatically".  The exponential-of-semicircle kernel
  * phi(z) = exp(beta (sqrt(1 - z^2) - 1)) on |z| <= 1 spans kernel_width
  * fine-grid cells; sigma is the fine-grid upsampling factor (2 or 1.25, the
- * two factors the paper reports for its FFTs, sec. 3.1). */
+ * two factors the paper reports for its FFTs, sec. 3.1).
+ * With tile, max_subproblem, spread_method and deterministic all zero, a
+ * call whose nodes reach only a small window of the fine grid (type 1 and
+ * type 3) spreads into registers and transforms that window by dense sums,
+ * without storing the fine grid; with every field zero, a small type-1 call
+ * is summed directly on the matrix cores. */
 typedef struct fh_options {
     double sigma;           /* 2.0 or 1.25 (in FH_MIXED, 1.25 amplifies the  *
                              * FP32 rounding near the band edge and suits    *
@@ -354,7 +359,8 @@ fh_status fh_field_targets(fh_ctx* ctx, const fh_quad* q, double lambda, double 
  * launch over every instance's work items, the FFT is one batched rocFFT
  * call, and for B > 1 the sequence is captured once into a hipGraph keyed by
  * the batch signature and replayed on later calls with the same signature
- * (B = 1 runs eagerly, as fh_field_grid). */
+ * (B = 1 runs eagerly, as fh_field_grid, and so does a batch whose nodes
+ * all reach only a small window of the fine grid; see fh_options). */
 fh_status fh_field_grid_batch(fh_ctx* ctx, int32_t B, const fh_quad* const* q,
                               const double* lambda, const double* z, int32_t n1, int32_t n2,
                               double h1, double h2, double xc, double yc,
@@ -485,7 +491,9 @@ fh_status fh_field_nsli_noalloc(fh_ctx* ctx, const double* X, const double* Y, c
  * context's tolerance; keep the fastest in the context and return it in
  * *best.  If cache_path is not NULL the result is read from / appended to
  * that JSON-lines file, keyed by precision, tolerance, grid size and node
- * count class. */
+ * count class.  The call as it runs without options is timed as well; where
+ * that is fastest, the context goes on to choose its path by itself (the
+ * file's field "automatic") and *best is the fastest set of options. */
 fh_status fh_autotune_grid(fh_ctx* ctx, const fh_quad* q, double lambda, double z, int32_t n1,
                            int32_t n2, double h1, double h2, const char* cache_path,
                            fh_options* best);
