@@ -120,6 +120,7 @@ class Batch:
         g = self.g
         t0 = time.perf_counter()
         o = self.ctx.autotune_batch(self.quads, self.lams, self.zs, g.n1, g.n2, g.h1, g.h2, cache_path=cache)
+        self.ctx.set_options(o)  # the options reported below, also where naming none was the fastest
         self.tuned = {"sigma": o.sigma, "tile": o.tile, "max_subproblem": o.max_subproblem,
                       "spread_method": o.spread_method, "tuning_s": time.perf_counter() - t0}
         return self.tuned

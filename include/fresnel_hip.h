@@ -492,8 +492,9 @@ fh_status fh_field_nsli_noalloc(fh_ctx* ctx, const double* X, const double* Y, c
  * *best.  If cache_path is not NULL the result is read from / appended to
  * that JSON-lines file, keyed by precision, tolerance, grid size and node
  * count class.  The call as it runs without options is timed as well; where
- * that is fastest, the context goes on to choose its path by itself (the
- * file's field "automatic") and *best is the fastest set of options. */
+ * that is fastest, the context keeps no options and goes on to choose its
+ * path by itself (the file's field "automatic"); *best is the fastest set of
+ * options that was named, for a context that is to keep them. */
 fh_status fh_autotune_grid(fh_ctx* ctx, const fh_quad* q, double lambda, double z, int32_t n1,
                            int32_t n2, double h1, double h2, const char* cache_path,
                            fh_options* best);

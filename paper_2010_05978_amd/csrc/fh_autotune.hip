@@ -103,9 +103,10 @@ fh_options merged(const fh_options& saved, const fh_options& t)
 }
 
 // Time `call` (which enqueues one field evaluation into u) for every
-// candidate that meets the context's tolerance; keep the fastest in the
-// context.  Each candidate runs twice untimed (for a batch: capture and a
-// first replay), then `reps` times between events.
+// candidate that meets the context's tolerance, and with nothing named; keep
+// the fastest in the context (*best: the fastest named options).  Each
+// candidate runs twice untimed (for a batch: capture and a first replay),
+// then `reps` times between events.
 template <class Call>
 fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vector<int>& tiles,
                const std::vector<int>& items, int reps, const std::string& key, const char* cache_path,
@@ -114,9 +115,8 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
     fh_options hit{};
     bool automatic = false;
     if (cache_lookup(cache_path, key, &hit, &automatic)) {
-        c->opt = merged(c->opt, hit);
-        c->tuned_auto = automatic;
-        *best = c->opt;
+        *best = merged(c->opt, hit);
+        c->opt = automatic ? merged(c->opt, fh_options{}) : *best;
         return FH_OK;
     }
     const fh_options saved = c->opt;
@@ -125,8 +125,6 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
     FH_HIP(hipEventCreate(&e1));
     const bool timing = c->timing;
     c->timing = false;
-    const bool saved_auto = c->tuned_auto;
-    c->tuned_auto = false;
     double best_ms = 1e300;
     fh_options best_o = saved;
     fh_status st = FH_OK;
@@ -194,12 +192,10 @@ fh_status tune(fh_ctx* c, int n, const std::vector<int>& methods, const std::vec
     (void)hipEventDestroy(e1);
     if (st != FH_OK) {
         c->opt = saved;
-        c->tuned_auto = saved_auto;
         return st;
     }
-    c->opt = best_o;
+    c->opt = automatic ? merged(saved, fh_options{}) : best_o;
     *best = best_o;
-    c->tuned_auto = automatic;
     cache_append(cache_path, key, best_o, best_ms, automatic);
     return FH_OK;
 }

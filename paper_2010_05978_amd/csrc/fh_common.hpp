@@ -223,10 +223,6 @@ struct fh_ctx {
     std::map<std::tuple<int, long long, int>, void*> poly_cache;  // (w, beta bits, precision)
     std::map<std::pair<int, int>, void*> lds_tw_cache;             // (LDS FFT length, real size)
     std::map<int, void*> roots_cache;  // roots of unity by order (roots_table)
-    // The autotuner found the automatic choice of path faster than every
-    // spread method with its options (fh_autotune_*): where the window path
-    // serves, it is taken although the options name a method.
-    bool tuned_auto = false;
     std::map<void*, size_t> owned;  // every hipMalloc'd block and its size
     double* bbox_dev = nullptr;      // bounding-box reduction scratch
     double* bbox_host = nullptr;     // pinned readback of the box

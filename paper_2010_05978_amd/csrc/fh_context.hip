@@ -773,7 +773,6 @@ fh_status fh_set_options(fh_ctx* c, const fh_options* opt)
     FH_ARG(c, FH_ERR_INVALID_ARG, "ctx is NULL");
     FH_TRY(check_options(opt));
     c->opt = opt ? *opt : fh_options{};
-    c->tuned_auto = false;
     return FH_OK;
 }
 

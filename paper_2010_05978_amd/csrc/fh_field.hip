@@ -257,7 +257,7 @@ bool window_plan(fh_ctx* c, const T1Plan& pl, int B, const fh_quad* const* qs, s
     st = FH_OK;
     const fh_options& o = c->opt;
     const bool automatic = o.spread_method == 0 && o.tile == 0 && o.max_subproblem == 0;
-    if (!(automatic || c->tuned_auto) || o.deterministic || pl.k.w > 16 || !pl.k.poly || B > 65535) return false;
+    if (!automatic || o.deterministic || pl.k.w > 16 || !pl.k.poly || B > 65535) return false;
     int SX = 16, SY = 16;
     for (int b = 0; b < B; ++b) {
         if (qs[b]->user_nodes || qs[b]->N == 0) return false;
