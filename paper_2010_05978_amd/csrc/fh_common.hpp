@@ -289,9 +289,10 @@ struct fh_quad {
     double D = 0.0;
     bool bbox_valid = false;
     double bbox[4] = {0, 0, 0, 0};  // xmin, xmax, ymin, ymax
-    // The nodes are the caller's own, in no order that is known (a generated
-    // rule's follow rays or arcs).
-    bool user_nodes = false;
+    // How far apart sixteen consecutive nodes lie (all but a few sixteens of
+    // the rule), in units of the box's largest coordinate: what the window
+    // spread has to know of the nodes' order.  Infinite: in no known order.
+    double near16 = INFINITY;
     // The boundary parameters of a rule built by one launch with its
     // parameters by value (radial curves and small polygons), from which a
     // batched call rebuilds it in place; null for the others.

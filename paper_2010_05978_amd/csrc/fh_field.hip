@@ -206,6 +206,19 @@ bool reach_cells(double lo, double hi, double s, int W, int nf, int& first, int&
     return true;
 }
 
+// Whether sixteen consecutive nodes start within the 17 - W cells of one
+// position of the window spread's accumulators, but for a few sixteens: those
+// that do not cost as much as sixteen.  Measured, 1e6 nodes on 512 x 512
+// outputs, tiled over window time against the extent in cells, W = 6, 8, 11,
+// 13 (T = 17 - W = 11, 9, 6, 4): all above 1.3 up to T - 1, 0.85 at 10.4 and
+// 11.5 (T = 11), 0.60 at 10.4 (T = 9), 0.41 to 0.9 from 6.7 on (T = 6), 0.81
+// at 4.7 (T = 4); mixed, W = 7 (T = 10): 2.2 and more up to 8.3, 0.74 at 11.5.
+bool near_enough(const fh_quad* q, const double* bb, double s1, double s2, int W)
+{
+    const double rho = std::max({std::fabs(bb[0]), std::fabs(bb[1]), std::fabs(bb[2]), std::fabs(bb[3])});
+    return q->near16 * rho * std::max(s1, s2) <= std::max(16.0 - W, 0.5);
+}
+
 // Workgroups per instance of the window spread: as many as are resident at
 // once, at least two batches of 64 nodes per wavefront.
 template <class R>
@@ -245,9 +258,8 @@ fh_status launch_win_spread(fh_ctx* c, int W, int B, const InstParams& p0, const
 // where it is narrow): few enough rows that the dense sums cost less than transforms
 // padded with zeros (8 flops per row and output; 2048 x 2048 outputs from 27
 // rows, FP64: 35 us against 122).  The matrix-core
-// spread needs the polynomial table and a kernel of at most 16 cells, and a
-// rule in its generator's order (any order is right, but sixteen consecutive
-// nodes far apart cost sixteen times the products).  Options that name a
+// spread needs the polynomial table and a kernel of at most 16 cells, and
+// rules in an order that suits it (near_enough; any order is right).  Options that name a
 // spread, a tile or an item size keep the tiled path, as does the
 // deterministic one, whose batches promise to run as they did.
 template <class R>
@@ -260,10 +272,10 @@ bool window_plan(fh_ctx* c, const T1Plan& pl, int B, const fh_quad* const* qs, s
     if (!automatic || o.deterministic || pl.k.w > 16 || !pl.k.poly || B > 65535) return false;
     int SX = 16, SY = 16;
     for (int b = 0; b < B; ++b) {
-        if (qs[b]->user_nodes || qs[b]->N == 0) return false;
+        if (qs[b]->N == 0) return false;
         double bb[4];
         st = quad_bbox(c, qs[b], bb);
-        if (st != FH_OK) return false;
+        if (st != FH_OK || !near_enough(qs[b], bb, inst[b].s1, inst[b].s2, pl.k.w)) return false;
         int l1, l2, s1, s2;
         if (!reach_cells(bb[0], bb[1], inst[b].s1, pl.k.w, pl.gg.nf1, l1, s1) ||
             !reach_cells(bb[2], bb[3], inst[b].s2, pl.k.w, pl.gg.nf2, l2, s2))
@@ -740,14 +752,14 @@ fh_status t3_core(fh_ctx* c, const fh_quad* q, double lambda, double z, int64_t 
     const bool lds2d = lr.C > 0 && lcol.C > 0;
     if (!lds2d) FH_TRY(fft_plan(c, d1.m, d2.m, 1, &fp));
     // A grid that a workgroup's LDS holds (up to 48 x 48 cells in FP64) is
-    // one window: the window spread takes a generated rule without binning,
+    // one window: the window spread takes a rule in order without binning,
     // slots and their merge (as window_plan, which gives the conditions; a
     // node's stencil never leaves the grid, which is planned that wide).
     // 998,400 nodes of a starshade on a 32 x 32 grid, 1e4 targets: FP64 at 1e-9
     // 176 -> 82 us, at 1e-12 242 -> 90, mixed 107 -> 52; 1e6 targets 281 -> 187.
     const fh_options& op = c->opt;
     const bool window = op.spread_method == 0 && op.tile == 0 && op.max_subproblem == 0 && !op.deterministic &&
-                        k.w <= 16 && k.poly && !q->user_nodes &&
+                        k.w <= 16 && k.poly && near_enough(q, sb, d1.s, d2.s, k.w) &&
                         win_lds(d1.nf, d2.nf, k.w, rs) <= kLdsBudget;
     WinGeom wg{d1.nf, d2.nf, d1.nf, d2.nf, 1};
     if (window) wg.nblk = win_blocks<R>(c, d1.nf, d2.nf, k.w, 1, N);

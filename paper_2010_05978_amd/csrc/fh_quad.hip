@@ -721,6 +721,36 @@ void set_bbox(fh_quad* q, double x0, double x1, double y0, double y1)
     q->bbox_valid = true;
 }
 
+// The part of (0, 1) over which sixteen consecutive ones of m Gauss-Legendre
+// nodes lie apart, and of the largest boundary coordinate over which sixteen
+// consecutive nodes of a dilation rule do (n boundary nodes in order, m nodes
+// a ray): a whole ray up to some twenty nodes, 20/m of it for longer ones (the
+// sixteens that end a ray and start the next are few then), and the boundary
+// nodes on the way.
+double ray_span(int m) { return m == 1 ? 0.0 : std::min(std::cos(0.75 * kPi / (m + 0.5)), 20.0 / m); }
+double dilation_near(int64_t n, int m) { return std::min(2.0, ray_span(m) + 30.0 * kPi / m / (double)n); }
+
+// The extent that all but 15% of the nodes of a rule keep to, from its parts'
+// node counts and extents.
+double most_near(std::vector<std::pair<double, int64_t>> parts)
+{
+    std::sort(parts.begin(), parts.end());
+    double N = 0.0, sum = 0.0;
+    for (const auto& p : parts) N += (double)p.second;
+    for (const auto& p : parts) {
+        sum += (double)p.second;
+        if (sum >= 0.85 * N) return p.first;
+    }
+    return 0.0;
+}
+
+// Disc and petals (rays of m nodes from a to R, np to a petal), in units of R.
+std::vector<std::pair<double, int64_t>> starshade_parts(int Np, double a, double R, int m, int np, int nd, int md)
+{
+    return {{a / R * dilation_near(std::max(nd, 1), md), (int64_t)nd * md},
+            {(R - a) / R * ray_span(m) + 30.0 * kPi / m / Np / np, (int64_t)Np * np * m}};
+}
+
 // A box holding every node of a dilation rule: each node is alpha (X_i, Y_i)
 // with 0 < alpha < 1, so the box of the boundary nodes and the origin holds
 // them all.  The boundary nodes are evaluated on the host at the rule's own
@@ -1049,6 +1079,9 @@ fh_status starshade_build(fh_ctx* c, int32_t Np, double a, double R, double b, d
     }
     // host inputs (and the across table) may be released on return
     if ((coef && coef_mem == FH_MEM_HOST) || Atab || mr >= 0) FH_HIP(hipStreamSynchronize(c->stream));
+    auto parts = starshade_parts(Np, a, R, m, np, nd, md);
+    if (mr >= 0) parts.push_back({(R - a) / R * ray_span(m), N - Npet});
+    qd->near16 = most_near(std::move(parts));
     // every node radius is at most R (edge perturbations move angles only)
     set_bbox(qd, -R, R, -R, R);
     *out = qd;
@@ -1097,6 +1130,7 @@ fh_status fh_quad_radial(fh_ctx* c, double r0, const double* a, const double* b,
             return s;
         }
         qd->rule = std::move(rec);
+        qd->near16 = dilation_near(n, m);
         // the box waits for a call that needs it (a type-1 row window)
         qd->host_box = [rp, n](double* box) { radial_box(rp, n, box); };
         *out = qd;
@@ -1124,6 +1158,7 @@ fh_status fh_quad_polygon(fh_ctx* c, const double* vx, const double* vy, int32_t
         const int64_t n = (int64_t)nv * q;
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, n * m, &qd));
+        qd->near16 = dilation_near(n, m);
         // nodes lie on segments from the origin to the boundary
         double bb[4] = {0.0, 0.0, 0.0, 0.0};
         for (int i = 0; i < nv; ++i) {
@@ -1192,6 +1227,9 @@ fh_status fh_quad_from_boundary(fh_ctx* c, const double* X, const double* Y, con
         FH_TRY(gl_table(c, m, &glm));
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, n * m, &qd));
+        // the boundary nodes' order is the caller's: only along a long ray is
+        // anything known
+        qd->near16 = m >= 16 ? dilation_near(std::max<int64_t>(n, 1), m) : 2.0;
         if (n == 0) {
             set_bbox(qd, 0.0, 0.0, 0.0, 0.0);
             *out = qd;
@@ -1349,6 +1387,9 @@ fh_status fh_quad_starshade_rigid(fh_ctx* c, int32_t Np, double a, double R, dou
             set_error("rigid-petal rule launch failed: %s", hipGetErrorString(e));
             return FH_ERR_HIP;
         }
+        auto parts = starshade_parts(Np, a, R, m, np, nd, md);
+        parts.push_back({2.0 * kPi * a / R / Np, Nb});
+        qd->near16 = most_near(std::move(parts));
         // rotations about the centre keep radii; translations add at most `shift`
         set_bbox(qd, -R - shift, R + shift, -R - shift, R + shift);
         *out = qd;
@@ -1371,7 +1412,6 @@ fh_status fh_quad_from_nodes(fh_ctx* c, const double* x, const double* y, const 
         FH_HIP(hipSetDevice(c->device));
         fh_quad* qd = nullptr;
         FH_TRY(quad_alloc(c, N, &qd));
-        qd->user_nodes = true;
         if (N > 0) {
             hipMemcpyKind kind = mem == FH_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
             FH_HIP(hipMemcpyAsync(qd->x, x, sizeof(double) * N, kind, c->stream));
@@ -1424,6 +1464,18 @@ fh_status fh_quad_koch(fh_ctx* c, int32_t L, const int32_t* p, fh_quad** out)
             set_error("k_koch_rule launch failed: %s", hipGetErrorString(e));
             return FH_ERR_HIP;
         }
+        // level k: triangles of side sqrt(3)/3^k, p rays of p nodes each; where
+        // sixteen nodes take several, those of neighbouring edges of the outline
+        // (of dimension log 4/log 3)
+        std::vector<std::pair<double, int64_t>> parts;
+        double side = std::sqrt(3.0);
+        for (int k = 0; k <= L; ++k, side /= 3.0) {
+            const double p2 = (double)p[k] * p[k];
+            const double own = std::min(1.0, ray_span(p[k]) + 15.0 / p2);
+            parts.push_back({side * (own + (p2 < 16.0 ? 3.0 * std::pow(16.0 / p2, 0.79) : 0.0)),
+                             kp.off[k + 1] - kp.off[k]});
+        }
+        qd->near16 = most_near(std::move(parts));
         // the snowflake lies in the unit disc
         set_bbox(qd, -1.0, 1.0, -1.0, 1.0);
         *out = qd;
@@ -1461,6 +1513,7 @@ fh_status fh_quad_fourier(fh_ctx* c, int32_t K, const double* ax, const double* 
             set_error("k_fourier_rule launch failed: %s", hipGetErrorString(e));
             return FH_ERR_HIP;
         }
+        qd->near16 = dilation_near(n, m);
         set_bbox(qd, box[0], box[1], box[2], box[3]);
         *out = qd;
         return FH_OK;
