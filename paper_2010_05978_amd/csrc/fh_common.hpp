@@ -119,12 +119,13 @@ struct InstParams {
     const double* w;
     int64_t N;
     int64_t node_off;  // first slot of this instance in the concatenated node range
-    int32_t tile_off;  // first tile id of this instance
+    int32_t tile_off;  // first tile id of this instance (window spread: its first workgroup)
     int32_t sh2;
     double pa, px, py, pc;
     double cx, cy, s1, s2;
     const double* src;
     int32_t sh1;       // first fine-grid column of the window (k_win_spread)
+    int32_t nblk;      // its workgroups (k_win_spread)
 };
 
 // Tiles need not divide the grid: the last tile of a row (of a column)

@@ -24,7 +24,8 @@ namespace {
 struct WinGeom {
     int nf1, nf2;
     int SX, SY;
-    int nblk;  // workgroups per instance
+    int nblk;  // workgroups of all instances
+    int run;   // nodes per wavefront, a multiple of 64
 };
 
 constexpr int kWinWaves = 4;  // wavefronts per workgroup
@@ -54,6 +55,20 @@ __device__ __forceinline__ int row_min16(int v)
 }
 __device__ __forceinline__ int row_max16(int v) { return -row_min16(-v); }
 
+// An instance in scalar registers: read from a table or the arguments by a
+// choice, the compiler keeps it in vector registers (57 spilled instead of 14
+// in k_win_spread at W = 11, and batches 15% slower).
+__device__ __forceinline__ InstParams uniform(const InstParams& p)
+{
+    union {
+        InstParams ip;
+        int w[sizeof(InstParams) / sizeof(int)];
+    } v{p};
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(InstParams) / sizeof(int)); ++k) v.w[k] = __builtin_amdgcn_readfirstlane(v.w[k]);
+    return v.ip;
+}
+
 // Spread without binning.  A wavefront walks a run of consecutive nodes, 64
 // at a time: a lane computes its node's cell, offsets and strength (as
 // k_bin_place does), then sixteen nodes at a time are staged and multiplied
@@ -67,10 +82,11 @@ __device__ __forceinline__ int row_max16(int v) { return -row_min16(-v); }
 // Bound by the operand staging (VALU and LDS), as k_spread_mfma; held to the
 // registers of four wavefronts per SIMD (14 spill in FP64; against three and
 // none, 86 and 88 us for 998,400 nodes on 2048 x 2048 outputs).
+// table, of_block: the instances and each workgroup's instance (null: p0's).
 template <class R, int W>
 __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_per_eu(4))) k_win_spread(
-    InstParams p0, const InstParams* __restrict__ table, WinGeom wg, typename V2<R>::T* __restrict__ part,
-    const R* __restrict__ poly)
+    InstParams p0, const InstParams* __restrict__ table, const int* __restrict__ of_block, WinGeom wg,
+    typename V2<R>::T* __restrict__ part, const R* __restrict__ poly)
 {
     using C = typename V2<R>::T;
     using M = MfmaAcc<R>;
@@ -98,10 +114,9 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
         reinterpret_cast<C*>(smem_raw)[e] = C{R(0), R(0)};
     for (int e = lane; e < RL; e += 64) rows[e] = R(0);
     __syncthreads();
-    const int b = blockIdx.y;
-    const InstParams ip = table ? table[b] : p0;
-    const int64_t share = ((ip.N + wg.nblk * kWinWaves - 1) / (wg.nblk * kWinWaves) + 63) / 64 * 64;
-    const int64_t n0 = min(ip.N, share * ((int64_t)blockIdx.x * kWinWaves + wv)), n1 = min(ip.N, n0 + share);
+    const InstParams ip = uniform(table ? table[of_block[blockIdx.x]] : p0);
+    const int64_t n0 = min(ip.N, (int64_t)wg.run * (((int)blockIdx.x - ip.tile_off) * kWinWaves + wv));
+    const int64_t n1 = min(ip.N, n0 + wg.run);
     int ox = 0, oy = 0;  // the accumulators' first cell, wavefront-uniform
     V are = V{R(0), R(0), R(0), R(0)}, aim = are;
     const uint32_t lane_off = (uint32_t)(i16 * sizeof(R));
@@ -225,7 +240,7 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     }
     move_to(0, 0);
     __syncthreads();
-    C* out = part + ((size_t)b * wg.nblk + blockIdx.x) * cells;
+    C* out = part + (size_t)blockIdx.x * cells;
     for (int e = threadIdx.x; e < cells; e += 64 * kWinWaves) {
         C v{R(0), R(0)};
 #pragma unroll
@@ -238,21 +253,23 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     }
 }
 
-// G[b] = the sum of instance b's nblk windows: 16 cells per workgroup, 16
+// G[b] = the sum of instance b's windows: 16 cells per workgroup, 16
 // threads a cell, each over every 16th window, then in thread order.  WRAP:
 // the window is a whole periodic grid from its cell (-nf1/2, -nf2/2) on (type
 // 3), and each sum goes to its place in the period.
 template <class R, bool WRAP>
-__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part, WinGeom wg,
+__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part, InstParams p0,
+                                                 const InstParams* __restrict__ table, WinGeom wg,
                                                  typename V2<R>::T* __restrict__ G)
 {
-    const int cells = wg.SX * wg.SY, nblk = wg.nblk;
+    const int cells = wg.SX * wg.SY;
+    const int nblk = table ? table[blockIdx.y].nblk : p0.nblk, blk0 = table ? table[blockIdx.y].tile_off : p0.tile_off;
     using C = typename V2<R>::T;
     __shared__ C s[16][17];
     const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4, b = blockIdx.y;
     C a{R(0), R(0)};
     if (e < cells) {
-        const C* p = part + (size_t)b * nblk * cells + e;
+        const C* p = part + (size_t)blk0 * cells + e;
 #pragma unroll 8
         for (int i = k; i < nblk; i += 16) {
             const C v = p[(size_t)i * cells];
