@@ -225,6 +225,12 @@ bool near_enough(const fh_quad* q, const double* bb, double s1, double s2, int W
 // instance).  With the same number for every instance an uneven batch waited
 // for its largest rule: 64 rules of 1e7 nodes in all on 256 x 256 outputs,
 // nine tenths of them in one, FP64 14.1 ms, and 0.61 so (equal rules 0.59).
+// In FP32 a run is also bounded, because its sum's rounding grows with it: at
+// 512 nodes the error is the tiled path's (5e7 nodes in one rule, type 3:
+// 4.5e-7, 4.7e-7 at 1024, 5.4e-7 at 2048, 2.8e-6 unbounded; that batch's
+// largest rule 2.6e-5 -> 2.1e-7), for 1.20 ms instead of 1.07.
+constexpr int64_t kWinRun32 = 512;
+
 template <class R>
 void win_blocks(const fh_ctx* c, WinGeom& wg, int W, int B, InstParams* inst)
 {
@@ -245,6 +251,7 @@ void win_blocks(const fh_ctx* c, WinGeom& wg, int W, int B, InstParams* inst)
         if (blocks(mid) > most) lo = mid + 1;
         else hi = mid;
     }
+    if (sizeof(R) == 4) lo = std::min(lo, kWinRun32 / 64);
     wg.run = (int)(64 * lo);
     wg.nblk = 0;
     for (int b = 0; b < B; ++b) {

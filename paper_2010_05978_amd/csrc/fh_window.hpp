@@ -254,7 +254,8 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
 }
 
 // G[b] = the sum of instance b's windows: 16 cells per workgroup, 16
-// threads a cell, each over every 16th window, then in thread order.  WRAP:
+// threads a cell, each over every 16th window, then in thread order, in
+// double (an FP32 rule of 5e7 nodes has 12,000 windows).  WRAP:
 // the window is a whole periodic grid from its cell (-nf1/2, -nf2/2) on (type
 // 3), and each sum goes to its place in the period.
 template <class R, bool WRAP>
@@ -265,9 +266,9 @@ __global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __rest
     const int cells = wg.SX * wg.SY;
     const int nblk = table ? table[blockIdx.y].nblk : p0.nblk, blk0 = table ? table[blockIdx.y].tile_off : p0.tile_off;
     using C = typename V2<R>::T;
-    __shared__ C s[16][17];
+    __shared__ double2 s[16][17];
     const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4, b = blockIdx.y;
-    C a{R(0), R(0)};
+    double2 a = make_double2(0.0, 0.0);
     if (e < cells) {
         const C* p = part + (size_t)blk0 * cells + e;
 #pragma unroll 8
@@ -288,9 +289,9 @@ __global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __rest
     if constexpr (WRAP) {
         const int r = e / wg.SX, c = e - r * wg.SX;
         const int y = r - wg.nf2 / 2, x = c - wg.nf1 / 2;
-        G[(size_t)(y < 0 ? y + wg.nf2 : y) * wg.nf1 + (x < 0 ? x + wg.nf1 : x)] = a;
+        G[(size_t)(y < 0 ? y + wg.nf2 : y) * wg.nf1 + (x < 0 ? x + wg.nf1 : x)] = C{(R)a.x, (R)a.y};
     } else {
-        G[(size_t)b * cells + e] = a;
+        G[(size_t)b * cells + e] = C{(R)a.x, (R)a.y};
     }
 }
 

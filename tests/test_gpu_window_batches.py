@@ -1,5 +1,6 @@
 """The window spread's split of a batch into workgroups: rules of very
-different sizes in one batch, and rules at the edges of a run of nodes."""
+different sizes in one batch, rules at the edges of a run of nodes, and the
+rounding of long rules in mixed precision."""
 import numpy as np
 import pytest
 
@@ -39,6 +40,29 @@ def test_largest_rule_of_an_uneven_batch_keeps_the_tolerance(fh):
         print(f"  rule {b} of {quads[b].N} nodes: {err:.1e}", flush=True)
         assert err <= 1e-5
     ctx.close()
+
+
+# 2e7 nodes in one rule: the error of the window path and of the tiled path,
+# whose items hold some 800 nodes each
+@pytest.mark.parametrize("points", [False, True], ids=["grid", "points"])
+def test_long_rules_round_as_the_tiled_path(fh, points):
+    n = 256
+    h = RADIUS * LAM * Z / (2 * n)
+    exact, ctx, other = tiled(fh, "fp64", tol=1e-12), fh.Context("mixed", tol=1e-5), tiled(fh, "mixed", tol=1e-5)
+    q = ctx.quad_radial(1.0, [0.05], [0.1], 0, 100_000, 200)
+    g = np.random.Generator(np.random.PCG64(22))
+    xi, eta = (torch.tensor(g.uniform(-0.5, 0.5, 3000), device="cuda") for _ in range(2))
+
+    def call(c):
+        u = c.field_points(q, 2 * LAM, Z, xi, eta) if points else c.field_grid(q, LAM, Z, n, n, h, h)
+        return u.to(torch.complex128)
+
+    want = call(exact)
+    err, base = (float((call(c) - want).norm() / want.norm()) for c in (ctx, other))
+    print(f"  window {err:.2e}, tiled {base:.2e}", flush=True)
+    assert err <= 1.25 * base
+    for c in (exact, ctx, other):
+        c.close()
 
 
 # an uneven batch takes no longer than its nodes do in equal rules (a factor
