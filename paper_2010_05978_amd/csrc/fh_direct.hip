@@ -145,17 +145,17 @@ __global__ void __launch_bounds__(256) k_direct(DirectParams p, typename V2<R>::
 
 // u = (sum of the splits' fields)/(i lambda z), 1 - u for an occulter: 16
 // outputs per workgroup, 16 threads each, every 16th split, then in thread
-// order.
+// order, in double (the splits' sums of FP32 products cancel).
 template <class R>
 __global__ void __launch_bounds__(256) k_direct_sum(const typename V2<R>::T* __restrict__ part, int64_t n,
                                                     int splits, double invlz, int occ,
                                                     typename V2<R>::T* __restrict__ u)
 {
     using C = typename V2<R>::T;
-    __shared__ C s[16][17];
+    __shared__ double2 s[16][17];
     const int64_t e = (int64_t)blockIdx.x * 16 + (threadIdx.x & 15);
     const int k = threadIdx.x >> 4;
-    C a{R(0), R(0)};
+    double2 a = make_double2(0.0, 0.0);
     if (e < n) {
 #pragma unroll 8
         for (int i = k; i < splits; i += 16) {
@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(256) k_direct_sum(const typename V2<R>::T* __r
         a.y += s[i][threadIdx.x].y;
     }
     // times 1/(i lambda z)
-    double re = (double)a.y * invlz, im = -(double)a.x * invlz;
+    double re = a.y * invlz, im = -a.x * invlz;
     if (occ) {
         re = 1.0 - re;
         im = -im;
@@ -183,13 +183,22 @@ __global__ void __launch_bounds__(256) k_direct_sum(const typename V2<R>::T* __r
 
 }  // namespace
 
-// Nodes times outputs (padded to blocks of 16) up to which the sum itself
-// takes less time than the tiled path, whose smallest call costs 45 us in
-// FP64 and 42 in mixed precision, all latency, and grows slowly.  Measured, in
-// us: FP64 14 at 1.0e7, 24 at 3.0e7, 33 at 6.2e7, 37 at 8.2e7, 48 at 1.25e8,
-// 55 at 1.3e8; mixed 11 at 1.0e7, 18 at 3.0e7, 28 at 8.2e7, 40 at 1.6e8, 59
-// to 76 at 2.5e8.
-constexpr double kDirectWork[2] = {1.0e8, 1.5e8};  // FP64, mixed
+// Up to where the sum itself takes less time than the tiled path, whose
+// smallest call costs 45 us in FP64 and 42 in mixed precision, all latency, and
+// grows slowly.  Two limits, since the sum's time has two parts.  The products:
+// nodes times outputs, padded to blocks of 16; in us, FP64 14 at 1.0e7, 24 at
+// 3.0e7, 33 at 6.2e7, 37 at 8.2e7, 48 at 1.25e8, 55 at 1.3e8; mixed 11 at
+// 1.0e7, 18 at 3.0e7, 28 at 8.2e7, 40 at 1.6e8, 59 to 76 at 2.5e8.  And the
+// staging, a sincos per node and coordinate of every 64 x 64 tile however few
+// outputs it holds, another per node where there are source terms or a point
+// source: nodes times outputs padded to 64, in us against the tiled path's,
+// FP64 45 : 50 at 2.6e8 and 58 : 76 to 89 at 4.1e8 (56 : 50 and 77 : 76 with
+// source terms), 190 : 134 at 1.6e9; mixed 39 : 45 at 2.0e8, 37 : 45 at
+// 2.6e8, 50 : 47 at 4.1e8 (31 : 47 at 1.4e8, 50 : 46 at 1.8e8), 175 : 76 at
+// 1.6e9.
+constexpr double kDirectWork[2] = {1.0e8, 1.5e8};   // FP64, mixed
+constexpr double kDirectStage[2] = {4.2e8, 2.8e8};
+constexpr double kDirectLit = 1.65;  // staging with source terms
 
 bool direct_serves(const fh_ctx* c, const fh_quad* q, int n1, int n2)
 {
@@ -202,8 +211,9 @@ bool direct_serves(const fh_ctx* c, const fh_quad* q, int n1, int n2)
         return false;
     const bool d = c->prec == FH_FP64;
     if (c->tol > (d ? 1.0001e-9 : 1.0001e-5)) return false;
-    const double out = (double)((n1 + 15) / 16 * 16) * ((n2 + 15) / 16 * 16);
-    return q->N > 0 && (double)q->N * out <= kDirectWork[d ? 0 : 1];
+    auto outputs = [&](int m) { return (double)((n1 + m - 1) / m * m) * ((n2 + m - 1) / m * m); };
+    const double stage = (q->src || q->D > 0.0 ? kDirectLit : 1.0) * (double)q->N * outputs(kDirTile);
+    return q->N > 0 && (double)q->N * outputs(16) <= kDirectWork[d ? 0 : 1] && stage <= kDirectStage[d ? 0 : 1];
 }
 
 template <class R>
