@@ -379,14 +379,18 @@ fh_status t1_window(fh_ctx* c, const T1Plan& pl, const WinGeom& wg, int B, const
     timing_mark(c, 3);
     // output rows per workgroup: up to 128, fewer while that leaves fewer
     // than two workgroups per CU (each repeats the columns' sum, which costs
-    // as much as SX rows)
+    // as much as SX rows) or their factors do not fit in LDS beside the window
     const int64_t cols = (n1 + 63) / 64;
     int KC = 128;
-    while (KC > 16 && cols * ((n2 + KC - 1) / KC) * B < 2 * (int64_t)c->cu_count) KC /= 2;
+    while (KC > 16 && (cols * ((n2 + KC - 1) / KC) * B < 2 * (int64_t)c->cu_count ||
+                       win_dft_lds(wg.SX, MT, KC, sizeof(R)) > kLdsBudget))
+        KC /= 2;
     const EpiParams ep{n1, n2, wg.nf1, wg.nf2, h1, h2, xc, yc, ip1, ip2};
     const dim3 dgrid((unsigned)cols, (n2 + KC - 1) / KC, B);
     const size_t dlds = win_dft_lds(wg.SX, MT, KC, sizeof(R));
-#define FH_WIN_DFT(mt)                                                                                            hipLaunchKernelGGL((k_win_dft<R, mt>), dgrid, dim3(256), dlds, c->stream, (const C2*)G, wg, u, ep, epi[0],                        etab, r1, r2, KC)
+#define FH_WIN_DFT(mt)                                                                                        \
+    hipLaunchKernelGGL((k_win_dft<R, mt>), dgrid, dim3(256), dlds, c->stream, (const C2*)G, wg, u, ep, epi[0], \
+                       etab, r1, r2, KC)
     switch (MT) {
     case 1: FH_WIN_DFT(1); break;
     case 2: FH_WIN_DFT(2); break;
