@@ -689,8 +689,6 @@ fh_status grid_vjp_impl(fh_ctx* c, const fh_quad* q, double lambda, double z, in
     if (dense) {
         using C2 = typename V2<R>::T;
         const double2 *r1 = nullptr, *r2 = nullptr;
-        FH_TRY(roots_table(c, gg.nf1, &r1));
-        FH_TRY(roots_table(c, gg.nf2, &r2));
         // rows per workgroup: 64, fewer while that leaves fewer than one
         // workgroup per CU (each repeats the columns' sum, which costs as much
         // as 48 rows)
@@ -698,21 +696,29 @@ fh_status grid_vjp_impl(fh_ctx* c, const fh_quad* q, double lambda, double z, in
         const int64_t ct = (n1 + 63) / 64;
         while (KC > 16 && ct * ((n2 + KC - 1) / KC) < (int64_t)c->cu_count) KC /= 2;
         const size_t cells = 3 * (size_t)gg.rows * span1, nwin = (size_t)ct * ((n2 + KC - 1) / KC);
-        FH_TRY(arena_reserve(c, aligned_bytes(sizeof(C2) * cells * nwin) + aligned_bytes(sizeof(C2) * cells)));
-        C2* part = c->arena.take<C2>(cells * nwin);
-        C2* F1 = c->arena.take<C2>(cells);
-        const AdjParams ap{n1, n2, gg.nf1, gg.nf2, gg.rows, ip.sh2, h1, h2, xc, yc, 0.5 / lz, occ ? -1.0 : 1.0, ip1,
-                           ip2};
-        timing_mark(c, 0);
-        timing_mark(c, 1);
-        timing_mark(c, 2);
-        FH_TRY(adj_window<R>(c, g_u, ap, span1, gg.rows, col0, r1, r2, part, KC, F1));
-        timing_mark(c, 3);
-        FH_TRY(launch_gather<R>(c, gg.W, reinterpret_cast<const R*>(F1), ip, gg, pl.k.beta, pl.k.poly, lz, acc, col0,
-                                span1, true, g_x, g_y, g_w));
-        timing_mark(c, 4);
-        timing_mark(c, 5);
-        return FH_OK;
+        fh_status s = roots_table(c, gg.nf1, &r1);
+        if (s == FH_OK) s = roots_table(c, gg.nf2, &r2);
+        if (s == FH_OK)
+            s = arena_reserve(c, aligned_bytes(sizeof(C2) * cells * nwin) + aligned_bytes(sizeof(C2) * cells));
+        // (on a narrow grid the workgroups' windows take more than the
+        // transforms' workspace, which may still fit a capped context)
+        if (s != FH_ERR_ALLOC) {
+            FH_TRY(s);
+            C2* part = c->arena.take<C2>(cells * nwin);
+            C2* F1 = c->arena.take<C2>(cells);
+            const AdjParams ap{n1, n2, gg.nf1, gg.nf2, gg.rows, ip.sh2, h1, h2, xc, yc, 0.5 / lz, occ ? -1.0 : 1.0,
+                               ip1, ip2};
+            timing_mark(c, 0);
+            timing_mark(c, 1);
+            timing_mark(c, 2);
+            FH_TRY(adj_window<R>(c, g_u, ap, span1, gg.rows, col0, r1, r2, part, KC, F1));
+            timing_mark(c, 3);
+            FH_TRY(launch_gather<R>(c, gg.W, reinterpret_cast<const R*>(F1), ip, gg, pl.k.beta, pl.k.poly, lz, acc,
+                                    col0, span1, true, g_x, g_y, g_w));
+            timing_mark(c, 4);
+            timing_mark(c, 5);
+            return FH_OK;
+        }
     }
     FftPlan* fa = nullptr;
     FftPlan* fb = nullptr;
