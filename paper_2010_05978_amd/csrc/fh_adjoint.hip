@@ -684,8 +684,18 @@ fh_status grid_vjp_impl(fh_ctx* c, const fh_quad* q, double lambda, double z, in
     }
     // a window that the LDS gather holds and that has up to 48 rows and
     // columns is evaluated densely: 8 (rows + rows columns/KC) flops per
-    // cotangent value and channel against two full transforms of zeros
-    const bool dense = span1 > 0 && gg.rows <= 48 && span1 <= 48 && adj_window_lds(gg.rows, span1, rs) > 0;
+    // cotangent value and channel against two full transforms of zeros.  On a
+    // small grid the dense sums' time is the chain of the window's 16 x 16
+    // blocks in a few workgroups, and the transforms' are short: with more
+    // than 2 x 2 blocks a gradient of 20,000 nodes takes, FP64, 41 to 44 us
+    // for 37 to 41 on 64^2 to 256^2 outputs, and 51 for 56 on 300^2; mixed 33
+    // to 36 for 30 to 33 and, on 512^2, 52 for 57; with up to 2 x 2, FP64, 31
+    // for 26 on 32^2, 31 for 31 on 64^2 and 31 for 36 on 64 x 500, mixed 18 for
+    // 22 and more everywhere.
+    const int blocks = ((gg.rows + 15) / 16) * ((span1 + 15) / 16);
+    const int64_t outputs = (int64_t)n1 * n2;
+    const bool pays = blocks > 4 ? outputs > 65536 : (rs == 4 || outputs >= 4096);
+    const bool dense = span1 > 0 && gg.rows <= 48 && span1 <= 48 && pays && adj_window_lds(gg.rows, span1, rs) > 0;
     if (dense) {
         using C2 = typename V2<R>::T;
         const double2 *r1 = nullptr, *r2 = nullptr;

@@ -1,7 +1,10 @@
 """The adjoint's dense window sums at their limits: a context whose capped
-memory holds the transforms' workspace only."""
+memory holds the transforms' workspace only, and the sizes of grid and window
+from which they are taken."""
 import numpy as np
 import pytest
+
+import oracle
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -28,3 +31,26 @@ def test_capped_workspace_falls_back_to_the_transforms(monkeypatch):
         assert err <= 1e-9
     ctx.close()
     free.close()
+
+
+# grids of fewer and of more than 4096 and 65536 outputs, windows of up to and of
+# more than 2 x 2 blocks of 16 cells (c cells in radius)
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-9), ("mixed", 1e-5)])
+@pytest.mark.parametrize("n1,n2", [(32, 32), (64, 62), (64, 64), (256, 256), (256, 258)])
+@pytest.mark.parametrize("c1,c2", [(3.0, 3.0), (8.0, 8.5), (3.0, 14.0), (14.0, 3.0)])
+def test_sides_of_the_size_rule(prec, tol, n1, n2, c1, c2):
+    import paper_2010_05978_amd as fh
+    ctx = fh.Context(prec, tol=tol)
+    lz = 0.25
+    h1, h2 = c1 * lz / (2 * n1), c2 * lz / (2 * n2)
+    args = (1.0, [0.1, 0.05], [0.0, 0.1], 3, 8, 9)
+    q, (x, y, w) = ctx.quad_radial(*args), oracle.quad_radial(*args)
+    g = np.random.Generator(np.random.PCG64([n1, n2, 3]))
+    gu = g.normal(size=(n2, n1)) + 1j * g.normal(size=(n2, n1))
+    xi, eta = oracle.grid_targets(n1, n2, h1, h2)
+    ref = oracle.fresnel_direct_vjp(x, y, w, lz, 1.0, xi, eta, gu.ravel())
+    got = ctx.field_grid_vjp(q, lz, 1.0, n1, n2, h1, h2, torch.tensor(gu, device="cuda").to(ctx.cdtype))
+    # within 20 times the field's tolerance, as in the other gradient tests
+    for a, b in zip(got, ref):
+        assert np.linalg.norm(a.cpu().numpy() - b) / np.linalg.norm(b) <= 20 * tol
+    ctx.close()
