@@ -1410,21 +1410,25 @@ inline size_t mfma_spread_lds(int NB, int T, int W, size_t rsize)
 // The slots of a tile with more than kMergeG work items are summed into its
 // first before the reduce.  A block takes kMergeChunk consecutive work items
 // at a time; where a crowded tile has items ra .. rb - 1 of its n among them,
-// the block sums all n slots over the share [LL ra/n, LL rb/n) of their
-// elements, so that a tile gets blocks in proportion to its slots and one
-// launch does what levels of groups would need two for.  A thread per
-// (lane of items, element): the lanes take every IL-th slot, sixteen loads in
-// flight, and are added in lane order.  Shares are disjoint, and the order of
-// every sum is fixed.
+// the block sums all n slots over the share [U ra/n, U rb/n) of their U units
+// of 128 bytes, so that a tile gets blocks in proportion to its slots (up to a
+// unit each) and one launch does what levels of groups would need two for.  A
+// thread per (lane of items, element): the lanes take every IL-th slot, sixteen
+// loads in flight, and are added in lane order.  Shares are disjoint, and the
+// order of every sum is fixed.
 // Chunks of 32 items with 256 threads, which leave a share of hundreds of
 // elements to lanes that walk a hundred slots each, were slower than two
 // launches of levels (the sweep of 50 x 60,000 targets 3.61 -> 3.72 ms);
 // chunks of 8 with 512 threads sum a crowded tile in a round or two of loads:
 // 3.56 -> 3.30 ms, one launch fewer, and the starfish on 1000 x 1000 88.9 ->
 // 82.1 us together with the row factors that moved into the scan's launch.
+// Shares of single elements read 16 bytes of a line at a time where a tile
+// holds a thousand slots (1e6 nodes in nine tiles, mixed, type 3: the call 147
+// us, 124 with units of 128 bytes, 126 with 64 and 139 with 256).
 constexpr int kMergeChunk = 8;
 constexpr int kMergeThreads = 512;
 constexpr int kMergeLoads = 16;  // loads in flight per thread
+constexpr int kMergeBytes = 128;  // a unit
 
 template <class R>
 __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T* __restrict__ slots,
@@ -1432,6 +1436,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
                                                      const int* __restrict__ tsub, int LL)
 {
     using C = typename V2<R>::T;
+    constexpr int64_t kUnit = kMergeBytes / sizeof(C);
     __shared__ int4 s_job[kMergeChunk];  // first slot, slots, first element, past the last
     __shared__ int s_n;
     __shared__ C s_acc[kMergeThreads];
@@ -1447,7 +1452,9 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
             if (n > kMergeG && (ra == 0 || threadIdx.x == 0)) {
                 const int rb = min(n, ra + kMergeChunk - (int)threadIdx.x);
                 const int m = atomicAdd(&s_n, 1);
-                s_job[m] = make_int4(first, n, (int)((int64_t)LL * ra / n), (int)((int64_t)LL * rb / n));
+                const int64_t units = (LL + kUnit - 1) / kUnit;
+                s_job[m] = make_int4(first, n, (int)min<int64_t>(LL, kUnit * (units * ra / n)),
+                                     (int)min<int64_t>(LL, kUnit * (units * rb / n)));
             }
         }
         __syncthreads();
