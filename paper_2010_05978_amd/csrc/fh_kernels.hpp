@@ -514,14 +514,19 @@ __global__ void k_rank_sorted(const uint32_t* __restrict__ key_sorted, const int
 // waves: FP64 binning 1.33 -> 1.30 ms on the batch).
 constexpr int kPlaceNodes = 4;
 
-// SCAN: the placement of a call of up to kPlaceScan tiles scans the counts
+// SCAN: the placement of a call of few tiles and nodes scans the counts
 // itself, every block all of them into its LDS, instead of waiting for a
 // launch of k_scan_tiles (one block, 3 to 4 us, and the gap before it, on the
 // path of a call that is all latency); block 0 writes the table of items for
 // the kernels that follow, and the row factors are blocks of this launch.
 // The starfish on 1000 x 1000 outputs 82.0 -> 80.6 us, 1e5 targets 60.8 ->
-// 59.8, the sweep of 50 x 60,000 targets 3.30 -> 3.24 ms.
+// 59.8, the sweep of 50 x 60,000 targets 3.30 -> 3.24 ms.  From some half a
+// million nodes on the launch is the cheaper: the tables leave half as many
+// blocks per CU, and every block scans (1e7 nodes, mixed: placement 126 ->
+// 164 us; whole calls at 1e5, 5e5, 1e6 and 5e6 nodes, 48.6 : 49.2, 68.9 : 68.9,
+// 91.6 : 90.6 and 276 : 261 us with and without).
 constexpr int kPlaceScan = 4096;
+constexpr int64_t kPlaceScanNodes = 1 << 19;
 
 template <class R, bool SCAN>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SCAN ? 4 : 5))) k_bin_place(InstParams p0, const InstParams* __restrict__ table,
@@ -2770,7 +2775,7 @@ fh_status spread_items(fh_ctx* c, const InstParams& p0, const InstParams* table,
         }
     }
     const unsigned nplace = nblocks(Ntot, 256 * kPlaceNodes);
-    if (Ntot > 0 && !table && !b.key && ntiles_total <= kPlaceScan) {
+    if (Ntot > 0 && Ntot <= kPlaceScanNodes && !table && !b.key && ntiles_total <= kPlaceScan) {
         hipLaunchKernelGGL((k_bin_place<R, true>), dim3(nplace + (rf.count > 0 ? nblocks(rf.count, 256) : 0)),
                            dim3(256), 0, c->stream, p0, table, (const int*)b.chunk, Ntot, gg, b.cnt, b.off, b.tsub,
                            b.rank, b.cell, (typename V2<R>::T*)b.dd, (typename V2<R>::T*)b.cc, b.subs, ntiles_total,
