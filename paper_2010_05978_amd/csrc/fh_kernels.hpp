@@ -1419,8 +1419,11 @@ inline size_t mfma_spread_lds(int NB, int T, int W, size_t rsize)
 // of 128 bytes, so that a tile gets blocks in proportion to its slots (up to a
 // unit each) and one launch does what levels of groups would need two for.  A
 // thread per (lane of items, element): the lanes take every IL-th slot, sixteen
-// loads in flight, and are added in lane order.  Shares are disjoint, and the
-// order of every sum is fixed.
+// loads in flight, and are added in lane order; sixteen slots are summed in R
+// and from there on in double, so that FP32 rounds as it did in groups of
+// sixteen (type 3 at upsampling 1.25, which amplifies it, 3e5 nodes: error
+// 8.5e-6, and 1.2e-5 with FP32 sums of whole lanes).
+// Shares are disjoint, and the order of every sum is fixed.
 // Chunks of 32 items with 256 threads, which leave a share of hundreds of
 // elements to lanes that walk a hundred slots each, were slower than two
 // launches of levels (the sweep of 50 x 60,000 targets 3.61 -> 3.72 ms);
@@ -1444,7 +1447,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
     constexpr int64_t kUnit = kMergeBytes / sizeof(C);
     __shared__ int4 s_job[kMergeChunk];  // first slot, slots, first element, past the last
     __shared__ int s_n;
-    __shared__ C s_acc[kMergeThreads];
+    __shared__ double2 s_acc[kMergeThreads];
     const int nsub = *nsub_ptr;
     for (int i0 = blockIdx.x * kMergeChunk; i0 < nsub; i0 += gridDim.x * kMergeChunk) {
         if (threadIdx.x == 0) s_n = 0;
@@ -1472,7 +1475,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
             for (int eb = 0; eb < ne; eb += kMergeThreads) {
                 const int w = min(ne - eb, kMergeThreads);  // elements of this pass (all of them when IL > 1)
                 const int il = (int)threadIdx.x / w, e = job.z + eb + (int)threadIdx.x - il * w;
-                C a{R(0), R(0)};
+                double2 a = make_double2(0.0, 0.0);
                 if (il < IL) {
                     const C* sp = slots + (size_t)job.x * LL + e;
                     for (int k = il; k < n; k += kMergeLoads * IL) {
@@ -1481,10 +1484,12 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
                         for (int u = 0; u < kMergeLoads; ++u)
                             v[u] = k + u * IL < n ? sp[(size_t)(k + u * IL) * LL] : C{R(0), R(0)};
 #pragma unroll
-                        for (int u = 0; u < kMergeLoads; ++u) {
-                            a.x += v[u].x;
-                            a.y += v[u].y;
+                        for (int u = 1; u < kMergeLoads; ++u) {
+                            v[0].x += v[u].x;
+                            v[0].y += v[u].y;
                         }
+                        a.x += v[0].x;
+                        a.y += v[0].y;
                     }
                 }
                 if (IL > 1) {
@@ -1492,12 +1497,12 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_slots(typename V2<R>::T
                     __syncthreads();
                     if (il == 0)
                         for (int k = 1; k < IL; ++k) {
-                            const C v = s_acc[k * w + threadIdx.x];
+                            const double2 v = s_acc[k * w + threadIdx.x];
                             a.x += v.x;
                             a.y += v.y;
                         }
                 }
-                if (il == 0) slots[(size_t)job.x * LL + e] = a;
+                if (il == 0) slots[(size_t)job.x * LL + e] = C{(R)a.x, (R)a.y};
                 __syncthreads();
             }
         }
