@@ -568,16 +568,17 @@ __global__ void __launch_bounds__(256) k_adj_win(const R* __restrict__ gu, AdjPa
 }
 
 // F[ch][r][c] = the sum of the n windows [ch][c][r]: 16 cells per workgroup,
-// 16 threads a cell, then in thread order.
+// 16 threads a cell, then in thread order, in double (a large grid has a
+// thousand windows).
 template <class R>
 __global__ void __launch_bounds__(256) k_adj_win_sum(const typename V2<R>::T* __restrict__ part, int SX, int SY,
                                                      int n, typename V2<R>::T* __restrict__ F)
 {
     using C = typename V2<R>::T;
-    __shared__ C s[16][17];
+    __shared__ double2 s[16][17];
     const int cells = SX * SY, total = 3 * cells;
     const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4;
-    C a{R(0), R(0)};
+    double2 a = make_double2(0.0, 0.0);
     if (e < total) {
 #pragma unroll 8
         for (int i = k; i < n; i += 16) {
@@ -595,7 +596,7 @@ __global__ void __launch_bounds__(256) k_adj_win_sum(const typename V2<R>::T* __
         a.y += s[i][threadIdx.x].y;
     }
     const int ch = e / cells, q = e - ch * cells, c = q / SY, r = q - c * SY;
-    F[(size_t)ch * cells + (size_t)r * SX + c] = a;
+    F[(size_t)ch * cells + (size_t)r * SX + c] = C{(R)a.x, (R)a.y};
 }
 
 // The three channels at the window's SY x SX cells from (sh2, col0), into F1.
