@@ -85,3 +85,22 @@ def test_autotuned(fh, tmp_path, sigma):
         assert binned(ctx, lambda: ctx.field_grid(q, LAM, Z, N, N, h, h)) != bool(automatic)
         ctx.close()
     first.close()
+
+
+# every kernel width that the matrix-core tile holds, on the window path (a
+# width that is named, not chosen by the tolerance, may have no polynomial table)
+@pytest.mark.parametrize("prec,digits", [("fp64", d) for d in range(1, 14)] + [("mixed", d) for d in range(2, 6)])
+def test_kernel_widths(fh, prec, digits):
+    o = dict(sigma=2.0, kernel_width=0, beta=0.0, tile=0, max_subproblem=0, deterministic=0)
+    ctx = fh.Context(prec, tol=10.0 ** -digits, options=fh.fh_options(spread_method=0, **o))
+    tiled = fh.Context(prec, tol=10.0 ** -digits, options=fh.fh_options(spread_method=2, **o))
+    q, h, ctx_tol = rule(ctx), spacing(2), 10.0 ** -digits
+    print(f"  width {ctx.query_params(N)['width']}", flush=True)
+    assert not binned(ctx, lambda: ctx.field_grid(q, LAM, Z, N, N, h, h))
+    u, v = (c.field_grid(q, LAM, Z, N, N, h, h) for c in (ctx, tiled))
+    # rounding of a million terms of total size pi/(lambda z) = 13, and the
+    # kernel's polynomials, whose error is a small part of the tolerance (the
+    # wavefront spread evaluates them per cell, the window spread in pairs)
+    assert float((u - v).abs().max()) <= 13.0 * (100.0 * (2.3e-16 if prec == "fp64" else 1.2e-7) + 1e-3 * ctx_tol)
+    tiled.close()
+    ctx.close()
