@@ -375,7 +375,7 @@ fh_status t1_window(fh_ctx* c, const T1Plan& pl, const WinGeom& wg, int B, const
     FH_TRY(launch_win_spread<R>(c, W, inst[0], tab, dblk, wg, part, pl.k.poly));
     timing_mark(c, 2);
     hipLaunchKernelGGL((k_win_sum<R, false>), dim3(nblocks(cells, 16), B), dim3(256), 0, c->stream,
-                       (const C2*)part, inst[0], tab, wg, G);
+                       (const C2*)part, tab, wg, G);
     timing_mark(c, 3);
     // output rows per workgroup: up to 128, fewer while that leaves fewer
     // than two workgroups per CU (each repeats the columns' sum, which costs
@@ -869,7 +869,7 @@ fh_status t3_core(fh_ctx* c, const fh_quad* q, double lambda, double z, int64_t 
         FH_TRY(launch_win_spread<R>(c, k.w, ip, nullptr, nullptr, wg, reinterpret_cast<C2*>(part), k.poly));
         timing_mark(c, 2);
         hipLaunchKernelGGL((k_win_sum<R, true>), dim3(nblocks((int64_t)d1.nf * d2.nf, 16)), dim3(256), 0, c->stream,
-                           reinterpret_cast<const C2*>(part), ip, (const InstParams*)nullptr, wg,
+                           reinterpret_cast<const C2*>(part), (const InstParams*)nullptr, wg,
                            reinterpret_cast<C2*>(fine));
         FH_HIP(hipGetLastError());
     } else {

@@ -55,8 +55,8 @@ __device__ __forceinline__ int row_min16(int v)
 }
 __device__ __forceinline__ int row_max16(int v) { return -row_min16(-v); }
 
-// An instance in scalar registers: read from a table or the arguments by a
-// choice, the compiler keeps it in vector registers (57 spilled instead of 14
+// An instance in scalar registers: the compiler keeps one that it reads from a
+// table at an index from memory in vector registers (57 spilled instead of 14
 // in k_win_spread at W = 11, and batches 15% slower).
 __device__ __forceinline__ InstParams uniform(const InstParams& p)
 {
@@ -114,7 +114,8 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
         reinterpret_cast<C*>(smem_raw)[e] = C{R(0), R(0)};
     for (int e = lane; e < RL; e += 64) rows[e] = R(0);
     __syncthreads();
-    const InstParams ip = uniform(table ? table[of_block[blockIdx.x]] : p0);
+    InstParams ip = p0;
+    if (table) ip = uniform(table[of_block[blockIdx.x]]);
     const int64_t n0 = min(ip.N, (int64_t)wg.run * (((int)blockIdx.x - ip.tile_off) * kWinWaves + wv));
     const int64_t n1 = min(ip.N, n0 + wg.run);
     int ox = 0, oy = 0;  // the accumulators' first cell, wavefront-uniform
@@ -253,29 +254,40 @@ __global__ void __launch_bounds__(64 * kWinWaves) __attribute__((amdgpu_waves_pe
     }
 }
 
-// G[b] = the sum of instance b's windows: 16 cells per workgroup, 16
-// threads a cell, each over every 16th window, then in thread order, in
-// double (an FP32 rule of 5e7 nodes has 12,000 windows).  WRAP:
-// the window is a whole periodic grid from its cell (-nf1/2, -nf2/2) on (type
-// 3), and each sum goes to its place in the period.
+// G[b] = the sum of instance b's windows (all of them without a table): 16
+// cells per workgroup, 16 threads a cell, each over every 16th window, then in
+// thread order, in double (an FP32 rule of 5e7 nodes has 24,000 windows).
+// WRAP: the window is a whole periodic grid from its cell (-nf1/2, -nf2/2) on
+// (type 3), and each sum goes to its place in the period.
 template <class R, bool WRAP>
-__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part, InstParams p0,
+__global__ void __launch_bounds__(256) k_win_sum(const typename V2<R>::T* __restrict__ part,
                                                  const InstParams* __restrict__ table, WinGeom wg,
                                                  typename V2<R>::T* __restrict__ G)
 {
     const int cells = wg.SX * wg.SY;
-    const int nblk = table ? table[blockIdx.y].nblk : p0.nblk, blk0 = table ? table[blockIdx.y].tile_off : p0.tile_off;
+    int nblk = wg.nblk, blk0 = 0;
+    if (table) {
+        nblk = table[blockIdx.y].nblk;
+        blk0 = table[blockIdx.y].tile_off;
+    }
     using C = typename V2<R>::T;
     __shared__ double2 s[16][17];
     const int e = blockIdx.x * 16 + (threadIdx.x & 15), k = threadIdx.x >> 4, b = blockIdx.y;
     double2 a = make_double2(0.0, 0.0);
     if (e < cells) {
         const C* p = part + (size_t)blk0 * cells + e;
-#pragma unroll 8
-        for (int i = k; i < nblk; i += 16) {
-            const C v = p[(size_t)i * cells];
-            a.x += v.x;
-            a.y += v.y;
+        // eight loads in flight, also where the count leaves a remainder (past
+        // the last window it is read again and adds nothing)
+        for (int i = k; i < nblk; i += 128) {
+            C v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = p[(size_t)min(i + 16 * q, nblk - 1) * cells];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const bool in = i + 16 * q < nblk;
+                a.x += in ? v[q].x : R(0);
+                a.y += in ? v[q].y : R(0);
+            }
         }
     }
     s[k][threadIdx.x & 15] = a;
