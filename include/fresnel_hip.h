@@ -75,9 +75,10 @@ typedef struct fh_targets fh_targets;
  * two factors the paper reports for its FFTs, sec. 3.1).
  * With tile, max_subproblem, spread_method and deterministic all zero, a
  * call whose nodes reach only a small window of the fine grid (type 1 and
- * type 3) spreads into registers and transforms that window by dense sums,
- * without storing the fine grid; with every field zero, a small type-1 call
- * is summed directly on the matrix cores. */
+ * type 3), in an order that keeps consecutive ones close, spreads into
+ * registers and transforms that window by dense sums, without storing the
+ * fine grid; with every field zero, a small type-1 call is summed directly on
+ * the matrix cores. */
 typedef struct fh_options {
     double sigma;           /* 2.0 or 1.25 (in FH_MIXED, 1.25 amplifies the  *
                              * FP32 rounding near the band edge and suits    *

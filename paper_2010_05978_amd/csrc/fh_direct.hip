@@ -35,8 +35,9 @@ struct DirectParams {
 // Sixteen-cell blocks past the grid's edge are skipped.
 // Bound by the chain staging, barrier, products (64 of 64 cycles in FP64),
 // barrier: a small call has two wavefronts per SIMD to overlap and two or
-// three stages each.  4800 nodes on 100 x 100 outputs, the whole call: 49 us
-// through the tiled path, 32 here (27 this kernel, 5 the sum of the splits).
+// three stages each.  4800 nodes on 100 x 100 outputs, one call among others:
+// 49 us through the tiled path, 28 here (traced apart, 27 this kernel and 5 the
+// sum of the splits).
 template <class R>
 __global__ void __launch_bounds__(256) k_direct(DirectParams p, typename V2<R>::T* __restrict__ part)
 {

@@ -213,6 +213,7 @@ bool reach_cells(double lo, double hi, double s, int W, int nf, int& first, int&
 // 13 (T = 17 - W = 11, 9, 6, 4): all above 1.3 up to T - 1, 0.85 at 10.4 and
 // 11.5 (T = 11), 0.60 at 10.4 (T = 9), 0.41 to 0.9 from 6.7 on (T = 6), 0.81
 // at 4.7 (T = 4); mixed, W = 7 (T = 10): 2.2 and more up to 8.3, 0.74 at 11.5.
+// (A 16-cell kernel has one position; half a cell then still serves most.)
 bool near_enough(const fh_quad* q, const double* bb, double s1, double s2, int W)
 {
     const double rho = std::max({std::fabs(bb[0]), std::fabs(bb[1]), std::fabs(bb[2]), std::fabs(bb[3])});
